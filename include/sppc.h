@@ -226,7 +226,7 @@ sppc_status sppc_setup(sppc_ctx** out, const sppc_csr* H, const int64_t* level_o
  * Y = H X for the matrix of the context (the paper's cost unit, Sec. IV.C).
  *   X_dev   row-major n x b, float64 (xt = SPPC_F64) or float32 (SPPC_F32)
  *   Y_dev   row-major n x b, float64
- *   b       1..32 (widths above 16 take the row-wise kernel over the full CSR)
+ *   b       1..32 (with the column-panel copy of H, widths above 16 go in column blocks of 16 and the rest)
  * float64 X uses the float64 values; float32 X uses the float32 values with
  * float32 products accumulated in float64.  Asynchronous on the context stream.
  */
@@ -256,10 +256,10 @@ sppc_status sppc_spmm_upper(const sppc_csr* H, const void* X_dev, sppc_dtype xt,
  * Y = H X exactly as sppc_spmm, for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): this call allocates
  * nothing.  When the context holds the column-panel copy of H and X is not already in the layout
- * its kernels read (b in {4, 8, 16} columns per row, 16-byte aligned), X is copied to a row stride
- * B = 4, 8 or 16 in the library's static device scratch array (32 MiB per device, held until the
+ * its kernels read (b in {1, 2, 4, 8, 16} columns per row, 16-byte aligned), X is copied to a row stride
+ * B = 1, 2, 4, 8 or 16 in the library's static device scratch array (32 MiB per device, held until the
  * process ends) instead of the context's buffer; n * B * sizeof(X element) beyond 32 MiB is
- * rejected with SPPC_E_ARG.  Every call on one device shares that array and it keeps the last
+ * rejected with SPPC_E_ARG (b > 16: the row-wise kernel, which needs no copy, takes the call).  Every call on one device shares that array and it keeps the last
  * call's contents: calls that overlap on one device (several streams or threads) race.
  * Arguments, layout and errors as sppc_spmm.
  */

@@ -859,7 +859,10 @@ void alloc_buffers(sppc_ctx* c, Arena& A) {
 }
 
 // Columns per panel of the column-panel copy of H (0: none): opts.panel_width, or automatically
-// 1 MiB of float64 X per panel when a k-column block of X exceeds 8 MiB and n < 2^24.
+// 1 MiB of float64 X per panel, at most 16384 columns, when a k-column block of X exceeds 8 MiB and
+// n < 2^24.  Narrow blocks gain nothing from wider panels (a longer run of a row's entries puts more
+// of an LDS add's lanes on one address): n = 1.17M, b = 1 1.12 ms with 65536 columns, 1.05 with 16384;
+// b = 2 1.16 and 1.10; b = 4 1.50 and 1.44.
 int choose_panel_width(const sppc_opts& o, int64_t n, int k) {
   int pw = o.panel_width;
   if (pw < 0) {
@@ -868,7 +871,7 @@ int choose_panel_width(const sppc_opts& o, int64_t n, int k) {
     if (xbytes > ((int64_t)8 << 20) && n < ((int64_t)1 << 24)) {
       int64_t w = ((int64_t)1 << 20) / ((int64_t)k * 8);  // 1 MiB of float64 X per panel
       int64_t p2 = 1024;
-      while (p2 * 2 <= w && p2 * 2 <= 65536) p2 *= 2;
+      while (p2 * 2 <= w && p2 * 2 <= 16384) p2 *= 2;
       pw = (int)p2;
     }
   }

@@ -530,66 +530,138 @@ __global__ void k_view_fill(int64_t n0, const int64_t* __restrict__ rp, const in
 // with all workgroups of a launch starting together, the panels of X they gather from stay in
 // L2 (the gathers are most of the product's time: without them it runs 1.5x faster).
 //
-// Inside a tile, group g of G lanes takes U = 8 consecutive entries (two vector loads of words
-// and values per lane, shared by the G lanes); lane h of the group gathers columns
-// [h*CPL, h*CPL + CPL) (CPL = 4) of each entry's row of X with 16-byte loads and adds the products
-// to the row's LDS accumulators (native float64 LDS adds).  In one add instruction the groups
-// hold entries 8 apart, which lie in different rows, so the adds rarely collide.  The words and
-// values of the tile D steps ahead are requested after the gathers of the current one.  X is
-// read from a copy with row stride B (16-byte aligned); the diagonal is not in the stream and is
-// added in float64 at the end: dg * X64 when X64 is given, else the product in the precision of
-// X.
+// Inside a tile, group g of G = B / CPL lanes takes U = 8 entries; lane h of the group gathers
+// columns [h*CPL, h*CPL + CPL) (CPL = min(B, 4)) of each entry's row of X with 16-byte loads and
+// adds the products to the row's LDS accumulators (native float64 LDS adds).  The words and values
+// of the tile D steps ahead are requested after the gathers of the current one, each stream byte by
+// one lane: the lanes of a group load a share of its 8 entries (G = 2, 4) and pass them on by DPP
+// moves, and a lane alone (G = 1) takes two runs of 4 entries so that the 64 lanes read consecutive
+// 16-byte pieces.  Letting every lane of a group load all 8 touched each line twice; the stream and
+// the gathers share the L1's line rate, which bounds the product (a random row of at most 128 bytes
+// costs 0.96 ns per CU from L2, whatever its size): n = 1.17M, d = 200, float64 X, b = 8 1.71 ->
+// 1.64 ms, b = 16 2.25 -> 2.16 ms, b = 1 1.08 -> 1.05 ms.  X is read from a copy with row stride B
+// (16-byte aligned); the diagonal is not in the stream and is added in float64 at the end: dg * X64
+// when X64 is given, else the product in the precision of X.
 
-template <typename VT> struct ValLoad;
-template <> struct ValLoad<float> {
-  static __device__ inline void load(const float* p, float (&v)[8]) {
-    const f32x4 a = __builtin_nontemporal_load((const f32x4*)p);
-    const f32x4 b = __builtin_nontemporal_load((const f32x4*)p + 1);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  }
+template <typename T, int N>
+struct alignas(sizeof(T) * N < 16 ? sizeof(T) * N : 16) Pack {
+  T v[N];
 };
-template <> struct ValLoad<double> {
-  static __device__ inline void load(const double* p, double (&v)[8]) {
+template <typename T, int N>  // nontemporal load of N consecutive values, in pieces of at most 16 bytes
+__device__ inline void stream_load(const T* p, T (&o)[N]) {
+  constexpr int W = sizeof(T) * N < 16 ? N : 16 / (int)sizeof(T);
+  typedef T V __attribute__((ext_vector_type(W)));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f64x2 a = __builtin_nontemporal_load((const f64x2*)p + i);
-      v[2 * i] = a.x;
-      v[2 * i + 1] = a.y;
+  for (int i = 0; i < N / W; ++i) {
+    const V a = __builtin_nontemporal_load((const V*)p + i);
+#pragma unroll
+    for (int q = 0; q < W; ++q) o[i * W + q] = a[q];
+  }
+}
+
+// CPL columns of one row of X
+template <typename XT, int CPL>
+__device__ inline Pack<XT, CPL> x_load(const XT* p) {
+  constexpr int W = sizeof(XT) * CPL < 16 ? CPL : 16 / (int)sizeof(XT);
+  Pack<XT, CPL> r;
+#pragma unroll
+  for (int i = 0; i < CPL / W; ++i) {
+    const Pack<XT, W> a = *((const Pack<XT, W>*)p + i);
+#pragma unroll
+    for (int q = 0; q < W; ++q) r.v[i * W + q] = a.v[q];
+  }
+  return r;
+}
+
+template <int CTRL>
+__device__ inline uint32_t dpp_get(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ inline float dpp_get(float x) {
+  return __uint_as_float(dpp_get<CTRL>(__float_as_uint(x)));
+}
+template <int CTRL>
+__device__ inline double dpp_get(double x) {
+  return __hiloint2double((int)dpp_get<CTRL>((uint32_t)__double2hiint(x)),
+                          (int)dpp_get<CTRL>((uint32_t)__double2loint(x)));
+}
+
+constexpr int PANEL_RB = 256;  // rows per block: the row index is stored in 8 bits
+constexpr int PANEL_U = 8;     // entries per lane group and tile
+
+// A lane's share of a group's 8 entries: 8 / G words and values.  e: the group's first entry; chunks
+// of 4 start at multiples of 4 and each block's stream is padded to 8, so a chunk that starts before
+// s1 is inside the allocation.  Beyond s1 the words are 0 (column 0: the gathers stay in bounds, the
+// adds are masked).
+template <int G, typename VT>
+struct PanelTile {
+  static constexpr int N = PANEL_U / G;
+  uint32_t w[N];
+  VT v[N];
+  // index of entry q of the group relative to e
+  static __device__ inline int at(int q) { return G == 1 ? (q & 3) + (q >> 2) * 256 : q; }
+  __device__ inline void load(const uint32_t* __restrict__ ent, const VT* __restrict__ pval, int64_t e, int64_t s1,
+                              int h) {
+    if constexpr (G == 1) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        uint32_t a[4] = {0u, 0u, 0u, 0u};
+        VT b[4] = {VT(0), VT(0), VT(0), VT(0)};
+        if (e + i * 256 < s1) {
+          stream_load<uint32_t, 4>(ent + e + i * 256, a);
+          stream_load<VT, 4>(pval + e + i * 256, b);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          w[4 * i + q] = a[q];
+          v[4 * i + q] = b[q];
+        }
+      }
+    } else if (e < s1) {
+      stream_load<uint32_t, N>(ent + e + N * h, w);
+      stream_load<VT, N>(pval + e + N * h, v);
+    } else {
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        w[q] = 0u;
+        v[q] = VT(0);
+      }
+    }
+  }
+  // the group's 8 entries in every one of its lanes
+  __device__ inline void expand(int h, uint32_t (&wd)[PANEL_U], VT (&cv)[PANEL_U]) const {
+    if constexpr (G == 1) {
+#pragma unroll
+      for (int q = 0; q < PANEL_U; ++q) {
+        wd[q] = w[q];
+        cv[q] = v[q];
+      }
+    } else if constexpr (G == 2) {  // swap with the partner (quad_perm 1, 0, 3, 2)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t ow = dpp_get<0xB1>(w[q]);
+        const VT ov = dpp_get<0xB1>(v[q]);
+        wd[q] = h ? ow : w[q];
+        wd[4 + q] = h ? w[q] : ow;
+        cv[q] = h ? ov : v[q];
+        cv[4 + q] = h ? v[q] : ov;
+      }
+    } else {  // lane p of the quad holds entries 2p and 2p + 1
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        wd[q] = dpp_get<0x00>(w[q]);
+        wd[2 + q] = dpp_get<0x55>(w[q]);
+        wd[4 + q] = dpp_get<0xAA>(w[q]);
+        wd[6 + q] = dpp_get<0xFF>(w[q]);
+        cv[q] = dpp_get<0x00>(v[q]);
+        cv[2 + q] = dpp_get<0x55>(v[q]);
+        cv[4 + q] = dpp_get<0xAA>(v[q]);
+        cv[6 + q] = dpp_get<0xFF>(v[q]);
+      }
     }
   }
 };
-
-struct f64x4 {
-  f64x2 lo, hi;
-};
-template <typename XT> struct XRow;  // CPL = 4 columns of one row of X (16 or 32 bytes)
-template <> struct XRow<float> {
-  static constexpr int CPL = 4;
-  typedef f32x4 V;
-  static __device__ inline V load(const float* p) { return *(const f32x4*)p; }
-  static __device__ inline float get(const V& v, int j) { return v[j]; }
-};
-template <> struct XRow<double> {
-  static constexpr int CPL = 4;
-  typedef f64x4 V;
-  static __device__ inline V load(const double* p) { return V{*(const f64x2*)p, *((const f64x2*)p + 1)}; }
-  static __device__ inline double get(const V& v, int j) { return j < 2 ? v.lo[j] : v.hi[j - 2]; }
-};
-
-constexpr int PANEL_RB = 256;  // rows per block: the row index is stored in 8 bits
-constexpr int PANEL_U = 8;     // consecutive entries per lane group and tile
-template <typename VT>
-__device__ inline void panel_load(const uint32_t* __restrict__ ent, const VT* __restrict__ pval, int64_t e,
-                                  int64_t s1, u32x4& wa, u32x4& wb, VT (&v)[PANEL_U]) {
-  if (e < s1) {
-    wa = __builtin_nontemporal_load((const u32x4*)(ent + e));
-    wb = __builtin_nontemporal_load((const u32x4*)(ent + e) + 1);
-    ValLoad<VT>::load(pval + e, v);
-  } else {
-    wa = u32x4{0u, 0u, 0u, 0u};  // column 0: the gathers stay in bounds, the adds are masked
-    wb = wa;
-  }
-}
 
 template <int B, int NW, int D, typename VT, typename XT>
 __global__ __launch_bounds__(NW * 64) void k_spmm_panel(int64_t n, const int64_t* __restrict__ bstart,
@@ -599,15 +671,15 @@ __global__ __launch_bounds__(NW * 64) void k_spmm_panel(int64_t n, const int64_t
                                                     double* __restrict__ Y, int64_t ldy, int b, int blk0,
                                                     const double* __restrict__ dg,
                                                     const double* __restrict__ X64, int64_t ldx64) {
-  typedef XRow<XT> XR;
-  constexpr int CPL = XR::CPL;
-  constexpr int G = B / CPL;       // lanes per entry
+  constexpr int CPL = B < 4 ? B : 4;
+  constexpr int G = B / CPL;       // lanes per entry: 1, 2 or 4
   constexpr int NG = 64 / G;       // entry groups per wave
   constexpr int U = PANEL_U;
   constexpr int T = NG * U;        // entries per wave tile
-  constexpr int YS = B + 1;        // LDS row stride in doubles (odd: spreads the rows over banks)
+  constexpr int YS = B + 1;        // LDS row stride in doubles (B even: spreads the rows over banks)
   constexpr int RB = PANEL_RB;
   constexpr int NT = NW * 64;      // threads
+  typedef PanelTile<G, VT> Tile;
   __shared__ double ysh[RB * YS];
   const int t = threadIdx.x;
   const int lane = t & 63, w = t >> 6;
@@ -621,38 +693,34 @@ __global__ __launch_bounds__(NW * 64) void k_spmm_panel(int64_t n, const int64_t
   const int64_t s1 = s0 + bcount[blk];
   const XT* xb = Xc + h * CPL;
   const int64_t step = (int64_t)NW * T;
-  int64_t e0 = s0 + (int64_t)w * T + g * U;  // this lane group's chunk of the current tile
-  // words and values of the next D tiles are in flight; chunks start at multiples of 8 and each
-  // block's stream is padded to 8, so a chunk that starts before s1 is inside the allocation
-  u32x4 wa[D], wb[D];
-  VT v[D][U];
+  int64_t tb = s0 + (int64_t)w * T;          // first entry of the current tile
+  int64_t e0 = tb + (G == 1 ? 4 : U) * g;    // this lane group's first entry in it
+  Tile tl[D];                                // the next D tiles are in flight
 #pragma unroll
-  for (int d = 0; d < D; ++d) panel_load(ent, pval, e0 + d * step, s1, wa[d], wb[d], v[d]);
-  int64_t tb = s0 + (int64_t)w * T;
+  for (int d = 0; d < D; ++d) tl[d].load(ent, pval, e0 + d * step, s1, h);
   while (tb < s1) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       if (tb >= s1) break;
-      const uint32_t wd[U] = {wa[d].x, wa[d].y, wa[d].z, wa[d].w, wb[d].x, wb[d].y, wb[d].z, wb[d].w};
-      typename XR::V xv[U];
-#pragma unroll
-      for (int q = 0; q < U; ++q) xv[q] = XR::load(xb + (int64_t)(wd[q] & 0xFFFFFFu) * B);
+      uint32_t wd[U];
       VT cv[U];
+      tl[d].expand(h, wd, cv);
+      Pack<XT, CPL> xv[U];
 #pragma unroll
-      for (int q = 0; q < U; ++q) cv[q] = v[d][q];
+      for (int q = 0; q < U; ++q) xv[q] = x_load<XT, CPL>(xb + (int64_t)(wd[q] & 0xFFFFFFu) * B);
       // loads return in issue order: the tile D steps ahead is requested after the gathers
       asm volatile("" ::: "memory");
-      panel_load(ent, pval, e0 + D * step, s1, wa[d], wb[d], v[d]);
+      tl[d].load(ent, pval, e0 + D * step, s1, h);
 #pragma unroll
       for (int q = 0; q < U; ++q) {
-        if (e0 + q < s1) {
+        if (e0 + Tile::at(q) < s1) {
           double* yr = ysh + (int)(wd[q] >> 24) * YS + h * CPL;
 #pragma unroll
           for (int j = 0; j < CPL; ++j) {
             if constexpr (sizeof(XT) == 4) {
-              atomicAdd(yr + j, (double)(cv[q] * XR::get(xv[q], j)));  // float32 product, float64 sum
+              atomicAdd(yr + j, (double)(cv[q] * xv[q].v[j]));  // float32 product, float64 sum
             } else {
-              atomicAdd(yr + j, (double)cv[q] * XR::get(xv[q], j));
+              atomicAdd(yr + j, (double)cv[q] * xv[q].v[j]);
             }
           }
         }
@@ -749,11 +817,18 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
     spmm_panel_rounds<B, 2, 2, VT, XT>(P, val, Xc, Y, ldy, b, sizeof(XT) == 4 ? 4 : 2, s, X64, ldx64);
 }
 
+// Widths above 16 go in column blocks of 16 and the rest, each through the copy of X.
 template <typename VT, typename XT>
 void launch_spmm_panel(const PanelH& P, const VT* val, const XT* X, int64_t ldx, double* Y, int64_t ldy, int b,
                        hipStream_t s, const double* X64 = nullptr, int64_t ldx64 = 0, void* stage = nullptr,
                        size_t stage_bytes = 0) {
-  if (b <= 4)
+  for (; b > 16; b -= 16, X += 16, Y += 16, X64 = X64 ? X64 + 16 : nullptr)
+    spmm_panel_b<16, VT, XT>(P, val, X, ldx, Y, ldy, 16, s, X64, ldx64, stage, stage_bytes);
+  if (b == 1)
+    spmm_panel_b<1, VT, XT>(P, val, X, ldx, Y, ldy, b, s, X64, ldx64, stage, stage_bytes);
+  else if (b == 2)
+    spmm_panel_b<2, VT, XT>(P, val, X, ldx, Y, ldy, b, s, X64, ldx64, stage, stage_bytes);
+  else if (b <= 4)
     spmm_panel_b<4, VT, XT>(P, val, X, ldx, Y, ldy, b, s, X64, ldx64, stage, stage_bytes);
   else if (b <= 8)
     spmm_panel_b<8, VT, XT>(P, val, X, ldx, Y, ldy, b, s, X64, ldx64, stage, stage_bytes);
@@ -1272,9 +1347,17 @@ void release_panel(PanelH& p) {
   p = PanelH{};
 }
 
+// Products that take the panel copy: no shift; widths 17..32 only where the copy of X they need
+// fits the given scratch (the row-wise kernel needs none).
+static bool use_panel(const DevCSR& H, int b, const double* shift, const void* stage, size_t stage_bytes,
+                      size_t elem) {
+  if (!H.panel || shift || b < 1 || b > 32 || H.n <= 0) return false;
+  return b <= 16 || !stage || (size_t)H.n * 16 * elem <= stage_bytes;
+}
+
 void spmm_f64(const DevCSR& H, const double* X, int64_t ldx, double* Y, int64_t ldy, int b,
               const double* shift, hipStream_t s, void* stage, size_t stage_bytes) {
-  if (H.panel && !shift && b >= 1 && b <= 16 && H.n > 0) {
+  if (use_panel(H, b, shift, stage, stage_bytes, sizeof(double))) {
     if (H.val64)
       launch_spmm_panel<double, double>(*H.panel, H.panel->val64, X, ldx, Y, ldy, b, s, nullptr, 0, stage,
                                         stage_bytes);
@@ -1294,7 +1377,7 @@ void spmm_f32(const DevCSR& H, const float* X, int64_t ldx, double* Y, int64_t l
               void* stage, size_t stage_bytes) {
   if (!H.val32) throw Error(1, "spmm_f32: no float32 values");
   if (diag && !X64) throw Error(1, "spmm_f32: the float64 diagonal term needs float64 X");
-  if (H.panel && !shift && b >= 1 && b <= 16 && H.n > 0) {
+  if (use_panel(H, b, shift, stage, stage_bytes, sizeof(float))) {
     // the panel stream holds the diagonal apart: diag * X64 in float64 when given, else the
     // float32 product as for the other entries
     launch_spmm_panel<float, float>(*H.panel, H.panel->val32, X, ldx, Y, ldy, b, s, diag ? X64 : nullptr,
