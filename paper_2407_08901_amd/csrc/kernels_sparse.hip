@@ -800,19 +800,21 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
     k_pad_copy<XT><<<(unsigned)cdiv(P.n * B, 256), 256, 0, s>>>(P.n, b, X, ldx, xp, B);
     Xc = xp;
   }
-  // Two launch shapes, words and values two tiles ahead in both: one-wave workgroups, four per
-  // CU, or two-wave workgroups, two (float64 X) or four (float32 X) per CU.  Measured per product
-  // (ms, one-wave / two-wave):
+  // Launch shapes, words and values two tiles ahead in all of them: one-wave workgroups, four per CU
+  // (eight for float32 X of width 8), or two-wave workgroups, two (float64 X) or four (float32 X) per
+  // CU.  Measured per product (ms, one-wave / two-wave):
   //   n = 7.72M, d = 300:  b = 4: 17.7 / 29.2 (float64 X), 14.0 / 21.1 (float32);
   //                        b = 8: 20.6 / 34.4, 18.5 / 25.5;  b = 16: two-wave 13-15% slower
-  //   n = 1.17M, d = 200:  b = 4: 1.53 / 1.90 (float64);  b = 8: 1.86 / 1.88 (float64),
-  //                        1.79 / 1.72 (float32);  b = 16: 2.79 / 2.64 (float64), 2.74 / 2.10
+  //   n = 1.17M, d = 200, float64 X:  b = 4: 1.44 / 1.89;  b = 8: 1.64 / 1.93;  b = 16: 2.16 / 2.09
+  //                       float32 X:  b = 1: 0.99 / 0.96;  b = 4: 1.20 / 1.29;  b = 8: 1.62 with four,
+  //                       1.49 with eight / 1.56;  b = 16: 2.13 / 1.90
   // The shape follows the rows, not the width of this product: a narrow product gathers as many
   // rows of X as a wide one.  One-wave workgroups when X at width 16 would exceed the 256 MB MALL
   // (its rows then come from HBM at longer latency, and more rows in flight per CU pay), and for
-  // float64 X of width <= 8.
-  if ((int64_t)P.n * 16 * (int64_t)sizeof(XT) > ((int64_t)256 << 20) || (sizeof(XT) == 8 && B <= 8))
-    spmm_panel_rounds<B, 1, 2, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
+  // widths up to 8, whose accumulators leave LDS for as many rows in flight.
+  const bool big = (int64_t)P.n * 16 * (int64_t)sizeof(XT) > ((int64_t)256 << 20);
+  if (big || B <= 8)
+    spmm_panel_rounds<B, 1, 2, VT, XT>(P, val, Xc, Y, ldy, b, !big && B == 8 && sizeof(XT) == 4 ? 8 : 4, s, X64, ldx64);
   else
     spmm_panel_rounds<B, 2, 2, VT, XT>(P, val, Xc, Y, ldy, b, sizeof(XT) == 4 ? 4 : 2, s, X64, ldx64);
 }
