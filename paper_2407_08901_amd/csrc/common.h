@@ -203,13 +203,17 @@ void project_out_block(int64_t n, int na, const int* idx, const double* Z, int64
 void paired_dots(int64_t n, int na, const int* idx, const double* Z, int64_t ldz, const double* T,
                  int64_t ldt, double* dots, double* work, hipStream_t s);
 
-// ---------------------------------------------------------------- small (kernels_small.hip)
+// ---------------------------------------------------------------- small (kernels_small.hip, kernels_eig.hip, kernels_eigblock.hip)
 
 // Lowest nwant eigenpairs of symmetric S (m x m, row-major lds): w[nwant] ascending,
 // V row-major m x nwant (ldv).  Single workgroup.  scratch >= eig_scratch(m, nwant) doubles.
 int64_t eig_scratch(int m, int nwant);
 void sym_eig_lowest(int m, int nwant, const double* S, int64_t lds, double* w, double* V,
                     int64_t ldv, double* scratch, hipStream_t s);
+
+// Every eigenpair of S (m <= 32), as the block iteration of the zeroth order needs them; arguments as
+// above.  sym_eig_lowest takes it whenever all pairs of such an S are wanted.
+void sym_eig_block(int m, const double* S, int64_t lds, double* w, double* V, int64_t ldv, hipStream_t s);
 
 // Orthonormalisation helpers (block of width b <= 32):
 // Step 1: from G = Phi^T Phi (b x b) and the squared norms of the original columns, drop
@@ -258,7 +262,7 @@ int64_t cg_work_doubles(int64_t n0);
 // doubles.
 void cg_prepare(const DevCSR& H0, int64_t n0, int64_t* rowb, double* tmp, hipStream_t s);
 // Deflated CG for the k small-space systems (b in r on entry, solution in x); ccoef = Ps^T b.
-// Products in float64 (float32-stored values are widened).  host_flag: two ints of pinned memory.
+// Products in float64 (float32-stored values are widened).  host_flag: 16 ints of pinned memory.
 int cg_solve(const DevCSR& H0, int64_t n0, int k, int D, const double* shift, const double* Ps,
              const int64_t* rowb, double* x, double* r, double* work, double* ccoef, int maxit, double tol,
              int* host_flag, hipStream_t s);

@@ -459,7 +459,7 @@ void small_solve(sppc_ctx* c, const double* shift = nullptr) {
   if (tol <= 0.0) tol = mixed ? 1e-6 : 1e-12;
   const double* sig = shift ? shift : c->E0;
   c->st.cg_iterations += cg_solve(c->H0, n0, k, D, sig, c->Psihat, c->cg_rowb, c->cx, c->cr, c->cgpart,
-                                  c->ccoef, 5000, tol, c->pin_i + 4, s);
+                                  c->ccoef, 5000, tol, c->pin_i + 64, s);
   deflate_coefs(D, k, c->E0, shift, c->ccoef, k, c->ctmp, k, s);
   gemm_nn(n0, D, k, c->Psihat, D, c->ctmp, k, c->cx, k, 1.0, 1.0, s);
   copy_block(n0, k, c->cx, k, c->Psi, k, s);
@@ -598,7 +598,7 @@ void small_expansion(sppc_ctx* c, const std::vector<int>& act) {
   jacobi_block(n, na, c->idx, c->R, k, c->diag, c->theta, c->Psi, na, s);
   gather_cols(n0, na, c->idx, c->R, k, c->cr, na, s);
   c->st.cg_iterations += cg_solve(c->H0, n0, na, D, c->cshift, c->Psihat, c->cg_rowb, c->cx, c->cr, c->cgpart,
-                                  c->ccoef, 1000, c->o.precond_tol, c->pin_i + 4, s);
+                                  c->ccoef, 1000, c->o.precond_tol, c->pin_i + 64, s);
   deflate_shift(D, na, c->E0, c->cshift, c->ccoef, na, c->ctmp, na, s);
   gemm_nn(n0, D, na, c->Psihat, D, c->ctmp, na, c->cx, na, 1.0, 1.0, s);
   copy_block(n0, na, c->cx, na, c->Psi, na, s);
