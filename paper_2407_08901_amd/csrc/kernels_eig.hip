@@ -2,14 +2,18 @@
 // one workgroup, Householder tridiagonalisation, multisection, inverse iteration, back-transformation.
 //
 // T is small (m <= 512, mostly <= 128), so every phase is a chain of dependent steps and the time is
-// latency: m = 64, 4 pairs 200 us, m = 128, 8 pairs 630 us before the form below.
-//   tridiagonalisation  the trailing block of at most 128 rows lives in the registers of 8 waves (wave w
-//                       holds rows w, w + 8, ...; lane i columns i and i + 64).  Each wave forms the
-//                       Householder vector for itself, so a step has one barrier (the 8 partial sums of
-//                       A v) instead of three; square root and divisions from the hardware
-//                       approximations with Newton steps.
+// latency: m = 64, 4 pairs 235 -> 163 us, m = 128, 8 pairs 630 -> 387 us against the form with three
+// barriers a step, a division per Sturm row and the vector in LDS.
+//   tridiagonalisation  the trailing block of at most 128 rows lives in the registers of 4 waves, one per
+//                       SIMD (wave w holds rows w, w + 4, ...; lane i columns i and i + 64).  Each wave
+//                       forms the Householder vector for itself, so a step has one barrier (the partial
+//                       sums of A v) instead of three; square root and divisions from the hardware
+//                       approximations with Newton steps.  A step is bound by the issue of its few hundred
+//                       dependent instructions: with two waves per SIMD the part that all waves repeat
+//                       costs twice (1.6 us a step at m = 64).  The wave's own entries of u, w and v are
+//                       read back from LDS as pairs: a readlane per entry costs more.
 //   multisection        Sturm counts by the three-term recurrence of the leading minors, rescaled every
-//                       8 steps: one dependent FMA per row instead of a division; 128 points a round.
+//                       8 steps: one dependent FMA per row instead of a division.
 //   inverse iteration   one lane per vector, operands of the next rows independent of the carried
 //                       values, reciprocal pivots kept; arrays interleaved by vector (no bank conflicts).
 //   back-transformation one wave per vector, its entries in registers.
@@ -63,115 +67,142 @@ __device__ inline void reflector(double alpha, double sigma, double& e, double& 
   if (alpha < 0.0) rv = -rv;
 }
 
-// Sturm counts (eigenvalues below x) of the tridiagonal (d, sqrt(e2)) at two points: sign changes of
-// the leading minors p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2}.  The matrix is scaled to norm < 1 and
-// e2 >= 1e-60, so 8 steps neither overflow nor underflow; a minor that is exactly zero takes the sign
-// opposite to its predecessor's.
-template <bool ZERO>
-__device__ inline double minor_step(double dd, double ee, double& p, double& pm, int& cnt) {
-  double pn = fma(dd, p, -(ee * pm));
-  if (ZERO && pn == 0.0) pn = p > 0.0 ? -1e-150 : 1e-150;
-  cnt += (int)(((uint32_t)(__double2hiint(pn) ^ __double2hiint(p))) >> 31);
-  pm = p;
-  p = pn;
-  return pn;
-}
-__device__ inline void minor_scale(double& p, double& pm) {
-  const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
-  p = ldexp(p, ex);
-  pm = ldexp(pm, ex);
-}
-__device__ __forceinline__ int2 sturm_pair(int m, const double* d, const double* e2, double x0, double x1) {
-  double p0 = 1.0, q0 = 0.0, p1 = 1.0, q1 = 0.0;
-  int c0 = 0, c1 = 0;
+// Sturm count (eigenvalues below x) of the tridiagonal (d, sqrt(e2)): sign changes of the leading minors
+// p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2}.  The matrix is scaled to norm < 1 and e2 >= 1e-34 (a coupling
+// of 1e-17, below the rounding of the norm), so 8 steps neither overflow nor underflow.  A minor that is
+// exactly zero counts as either sign: the next has the sign opposite to its predecessor's.  Rows beyond m
+// (up to a multiple of 8) hold d = 4, which changes no sign.
+__device__ __forceinline__ int sturm_count(int m, const double* d, const double* e2, double x) {
+  double p = 1.0, pm = 0.0;
+  uint32_t sg = 0;  // signs of the minors, the latest in bit 0
+  int cnt = 0;
   for (int i = 0; i < m; i += 8) {
     double dd[8], ee[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int r = min(i + u, m - 1);
-      dd[u] = d[r];
-      ee[u] = r > 0 ? e2[r - 1] : 0.0;
+      dd[u] = d[i + u] - x;
+      ee[u] = e2[i + u];
     }
-    const double sp0 = p0, sq0 = q0, sp1 = p1, sq1 = q1;
-    const int sc0 = c0, sc1 = c1;
-    bool zero = false;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      if (i + u < m) {
-        zero |= minor_step<false>(dd[u] - x0, ee[u], p0, q0, c0) == 0.0;
-        zero |= minor_step<false>(dd[u] - x1, ee[u], p1, q1, c1) == 0.0;
-      }
+      const double pn = fma(dd[u], p, -(ee[u] * pm));
+      pm = p;
+      p = pn;
+      sg = __builtin_amdgcn_alignbit(sg, (uint32_t)__double2hiint(pn), 31);
     }
-    if (zero) {
-      p0 = sp0, q0 = sq0, p1 = sp1, q1 = sq1;
-      c0 = sc0, c1 = sc1;
-      for (int u = 0; u < 8; ++u) {
-        if (i + u < m) {
-          minor_step<true>(dd[u] - x0, ee[u], p0, q0, c0);
-          minor_step<true>(dd[u] - x1, ee[u], p1, q1, c1);
-        }
-      }
-    }
-    minor_scale(p0, q0);
-    minor_scale(p1, q1);
+    cnt += __popc((sg ^ (sg >> 1)) & 0xFFu);
+    const int f = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
+    p = ldexp(p, f);
+    pm = ldexp(pm, f);
   }
-  return make_int2(c0, c1);
+  return cnt;
 }
 
 // Two solves (Tri - lam I) y = y by Gaussian elimination with partial pivoting, from a random start
 // (the shift is the eigenvalue to a few ulp: two suffice).  Row k of this vector: index k * nw of the
-// arrays; r0 = 1 / u0, u2 = e[k + 1] where the rows were interchanged.
-__device__ __forceinline__ void inverse_iteration(int m, int nw, const double* d, const double* e, double lam, double epsp,
-                                  uint32_t seed, double* __restrict__ u1, double* __restrict__ l,
-                                  double* __restrict__ r0, double* __restrict__ y, unsigned char* __restrict__ piv) {
+// arrays; r0 = 1 / u0, u2 = e[k + 1] where the rows were interchanged.  Rows go in batches of B whose
+// operands are loaded together and whose results are stored together, so that the chain of carried
+// values waits for LDS once a batch.
+template <int B>
+__device__ __forceinline__ void inverse_iteration(int m, int nw, const double* d, const double* e, double lam,
+                                                  double epsp, uint32_t seed, double* u1, double* l, double* r0,
+                                                  double* y, unsigned char* piv) {
   uint32_t h = seed;
-  auto start = [&]() {
-    h ^= h << 13; h ^= h >> 17; h ^= h << 5;
-    return 0.5 + (double)(h & 0xFFFFFF) / (double)0x1000000;
+  auto start = [&]() {  // in [0.5, 1)
+    h = h * 1664525u + 1013904223u;
+    return __hiloint2double((int)(0x3FE00000u | (h >> 12)), 0);
   };
   auto away = [&](double a) { return fabs(a) < epsp ? (a >= 0.0 ? epsp : -epsp) : a; };
   double ca = d[0] - lam, cb = m > 1 ? e[0] : 0.0, cur = start();
-#pragma unroll 4
-  for (int k = 0; k < m - 1; ++k) {
-    const double sub = e[k], na = d[k + 1] - lam, nb = k + 2 < m ? e[k + 1] : 0.0, yn = start();
-    const bool sw = fabs(ca) < fabs(sub);
-    const double pv = away(sw ? sub : ca);
-    double r = __builtin_amdgcn_rcp(pv);
-    r = fma(r, fma(-pv, r, 1.0), r);
-    const double mult = (sw ? ca : sub) * r;
-    const double a1 = sw ? na : cb;
-    const double yk = sw ? yn : cur;
-    cur = fma(-mult, yk, sw ? cur : yn);
-    ca = fma(-mult, a1, sw ? cb : na);
-    cb = sw ? -mult * nb : nb;
-    u1[k * nw] = a1;
-    l[k * nw] = mult;
-    r0[k * nw] = r;
-    y[k * nw] = yk;
-    piv[k * nw] = sw;
+  for (int k0 = 0; k0 < m - 1; k0 += B) {
+    double ee[B + 1], na[B], b1[B], bl[B], br[B], by[B];
+    unsigned swb = 0;
+#pragma unroll
+    for (int u = 0; u < B + 1; ++u) ee[u] = e[min(k0 + u, m - 1)];  // e[m - 1] = 0
+#pragma unroll
+    for (int u = 0; u < B; ++u) na[u] = d[min(k0 + u + 1, m - 1)] - lam;
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (k0 + u < m - 1) {
+        const double yn = start();
+        const bool sw = fabs(ca) < fabs(ee[u]);
+        const double pv = away(sw ? ee[u] : ca);
+        double r = __builtin_amdgcn_rcp(pv);
+        r = fma(r, fma(-pv, r, 1.0), r);
+        const double mult = (sw ? ca : ee[u]) * r;
+        b1[u] = sw ? na[u] : cb;
+        by[u] = sw ? yn : cur;
+        cur = fma(-mult, by[u], sw ? cur : yn);
+        ca = fma(-mult, b1[u], sw ? cb : na[u]);
+        cb = sw ? -mult * ee[u + 1] : ee[u + 1];
+        bl[u] = mult;
+        br[u] = r;
+        swb |= sw ? 1u << u : 0u;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (k0 + u < m - 1) {
+        const int q = (k0 + u) * nw;
+        u1[q] = b1[u];
+        l[q] = bl[u];
+        r0[q] = br[u];
+        y[q] = by[u];
+        piv[q] = (swb >> u) & 1u;
+      }
+    }
   }
   const double rl = fast_rcp(away(ca));
   for (int it = 0; it < 2; ++it) {
     if (it == 1) {
       cur = y[0];
-#pragma unroll 4
-      for (int k = 0; k < m - 1; ++k) {
-        const double yn = y[(k + 1) * nw], mult = l[k * nw];
-        const bool sw = piv[k * nw];
-        const double yk = sw ? yn : cur;
-        cur = fma(-mult, yk, sw ? cur : yn);
-        y[k * nw] = yk;
+      for (int k0 = 0; k0 < m - 1; k0 += B) {
+        double yn[B], ml[B];
+        bool sw[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          const int q = min(k0 + u, m - 2) * nw;
+          yn[u] = y[q + nw];
+          ml[u] = l[q];
+          sw[u] = piv[q];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          if (k0 + u < m - 1) {
+            const double yk = sw[u] ? yn[u] : cur;
+            cur = fma(-ml[u], yk, sw[u] ? cur : yn[u]);
+            yn[u] = yk;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+          if (k0 + u < m - 1) y[(k0 + u) * nw] = yn[u];
       }
     }
     double y1 = cur * rl, y2 = 0.0;
     y[(m - 1) * nw] = y1;
-#pragma unroll 4
-    for (int k = m - 2; k >= 0; --k) {
-      const double a2 = k + 2 < m && piv[k * nw] ? e[k + 1] : 0.0;
-      const double v = fma(-u1[k * nw], y1, fma(-a2, y2, y[k * nw])) * r0[k * nw];
-      y2 = y1;
-      y1 = v;
-      y[k * nw] = v;
+    for (int k0 = m - 2; k0 >= 0; k0 -= B) {
+      double a1[B], a2[B], rr[B], yk[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int k = max(k0 - u, 0), q = k * nw;
+        a1[u] = u1[q];
+        rr[u] = r0[q];
+        yk[u] = y[q];
+        a2[u] = piv[q] ? e[k + 1] : 0.0;  // (e[m - 1] = 0)
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        if (k0 - u >= 0) {
+          const double v = fma(-a1[u], y1, fma(-a2[u], y2, yk[u])) * rr[u];
+          y2 = y1;
+          y1 = v;
+          yk[u] = v;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (k0 - u >= 0) y[(k0 - u) * nw] = yk[u];
     }
   }
 }
@@ -267,16 +298,27 @@ __device__ __forceinline__ void eig_vectors(int m, int nw, const double* lam, do
       y[0][q] = i < m ? Yn[(int64_t)c * m + i] : 0.0;
       y[1][q] = i < m ? Yn[(int64_t)cb * m + i] : 0.0;
     }
-    for (int j = m - 3; j >= 0; --j) {
-      const double b = bl[j];
-      // entry j + 1 of v_j: index (a sum that stays non-negative in every part)
+    // the vector of step j is requested a step ahead (v_j: entries j + 1..; an index that stays
+    // non-negative in every part)
+    auto vec_of = [&](int j, double (&x)[NR]) {
       const int v0 = HVL ? j * (m - 1) - j * (j - 1) / 2 : j * m + j + 1;
-      double x[NR], s0 = 0.0, s1 = 0.0;
 #pragma unroll
       for (int q = 0; q < NR; ++q) {
         const int i = ln + 64 * q;
         x[q] = 0.0;
         if (i > j && i < m) x[q] = HVL ? hv[v0 + (i - j - 1)] : A[v0 + (i - j - 1)];
+      }
+    };
+    double xn[NR];
+    if (m >= 3) vec_of(m - 3, xn);
+    for (int j = m - 3; j >= 0; --j) {
+      const double b = bl[j];
+      double x[NR], s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) x[q] = xn[q];
+      if (j > 0) vec_of(j - 1, xn);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
         s0 = fma(x[q], y[0][q], s0);
         s1 = fma(x[q], y[1][q], s1);
       }
@@ -329,11 +371,15 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
                                                  double* __restrict__ wout, double* __restrict__ V, int64_t ldv,
                                                  double* __restrict__ scr) {
   constexpr bool HEAD = NTH > 512;
-  constexpr int LDV = HEAD ? EIG_MAX : EIG_T;
+  constexpr int TW = HEAD ? 8 : 4;     // waves that hold the trailing block (128 registers a lane cap HEAD's)
+  constexpr int RW = EIG_T / TW;       // rows a wave holds
+  constexpr int RL = 64 / TW;          // its rows below 64
+  constexpr int GR = HEAD ? 4 : 8;     // rows taken together
+  constexpr int LDV = (HEAD ? EIG_MAX : EIG_T) + 8;
   __shared__ double buf[EIG_BUF];
   __shared__ double vec[(HEAD ? 7 : 6) * LDV];
   __shared__ double sc;
-  const int t = threadIdx.x, w = t >> 6, ln = t & 63;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), ln = t & 63;
   double* const A = scr;
   double* const dg = scr + (int64_t)m * m;
   double* const eg = dg + m;
@@ -437,19 +483,20 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
     }
   }
 
-  // ---- the trailing block, rows o.. of T, in the registers of waves 0..7
+  // ---- the trailing block, rows o.. of T, in the registers of waves 0..TW-1
   const int L = m - o;
   double* const hv = buf;                   // packed v_j, j = 0..L-3
-  double* const pp = buf + EIG_HV;          // [2][8][128] partial sums of A v by step parity
-  double* const rowb = pp + 2 * 8 * EIG_T;  // [2][128] the next row, by step parity
-  double* const own = rowb + 2 * EIG_T;     // [8][3][16] per wave: v, v', w at its own rows
-  double a[16][2], u[2] = {0.0, 0.0}, wr[2] = {0.0, 0.0};
-  if (w < 8) {
+  double* const pp = buf + EIG_HV;          // [2][TW][128] partial sums of A v by step parity
+  double* const rowb = pp + 2 * TW * EIG_T;  // [2][128] the next row, by step parity
+  double* const own = rowb + 2 * EIG_T;     // [TW][3][RW] per wave: u, w and v at its own rows
+  double* const kps = own + TW * 3 * RW;    // [2][TW] partial sums of v^T A v, by step parity
+  double a[RW][2], u[2] = {0.0, 0.0}, wr[2] = {0.0, 0.0};
+  if (w < TW) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
+    for (int r = 0; r < RW; ++r)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const int l = w + 8 * r, i = ln + 64 * c;
+        const int l = w + TW * r, i = ln + 64 * c;
         double x = 0.0;
         if (l < L && i < L) {
           if constexpr (HEAD) {
@@ -467,8 +514,7 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
       rowb[ln] = a[0][0];
       rowb[64 + ln] = a[0][1];
     }
-    double* ow = own + w * 48;
-    if (ln < 48) ow[ln] = 0.0;
+    for (int i = ln; i < 3 * RW; i += 64) own[w * 3 * RW + i] = 0.0;
   }
   __syncthreads();
   if constexpr (HEAD) {
@@ -481,7 +527,7 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
   const bool two = L > 64;
   for (int j = 0; j + 2 < L; ++j) {
     double v[2] = {0.0, 0.0}, b = 0.0;
-    if (w < 8) {
+    if (w < TW) {
       const double* rb = rowb + (j & 1) * EIG_T;
       const double uj = lane_get(j < 64 ? u[0] : u[1], j & 63), wj = lane_get(j < 64 ? wr[0] : wr[1], j & 63);
       double x[2];
@@ -507,71 +553,100 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
           bl[o + j] = b;
         }
       }
-      if (w == (j & 7)) {
+      if (w == j % TW) {
         double* dst = hv + j * (L - 1) - j * (j - 1) / 2 - (j + 1);
         if (ln > j && ln < L) dst[ln] = v[0];
         if (two && ln + 64 > j && ln + 64 < L) dst[ln + 64] = v[1];
       }
-      double* ow = own + w * 48;
-      double* const ov = ow + 16 * (j & 1);
-      const double* const ou = ow + 16 * ((j & 1) ^ 1);
-      const double* const owr = ow + 32;
-      if ((ln & 7) == w) {
-        ov[ln >> 3] = v[0];
-        ov[8 + (ln >> 3)] = v[1];
+      // apply the pending update of step j - 1 to this wave's rows and form its part of A v, GR rows
+      // at a time; the rows' own entries of u, w and v come from LDS (u and w written in the step before),
+      // the next rows' requested ahead where registers allow.  (Rows up to j: v is zero there, and they are read no more.)
+      double* const ow = own + w * 3 * RW;
+      if (ln % TW == w) {
+        ow[2 * RW + ln / TW] = v[0];
+        ow[2 * RW + RL + ln / TW] = v[1];
       }
       wave_lds_fence();
-      // apply the pending update of step j - 1 to the rows below j and form this wave's part of A v
       double s0 = 0.0, s1 = 0.0;
-      double* nrow = rowb + ((j + 1) & 1) * EIG_T;
+      double* const nrow = rowb + ((j + 1) & 1) * EIG_T;
+      const int g1 = (L - w + GR * TW - 1) / (GR * TW);  // groups of GR rows that this wave holds
+      const int g0 = j >= w ? (j - w) / TW / GR : 0;      // first one with a row beyond j
+      double ul[GR], wl[GR], vl[GR];
+      auto own_rows = [&](int g, double (&ul_)[GR], double (&wl_)[GR], double (&vl_)[GR]) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int l = w + 8 * r;
-        if (l > j && l < L) {
-          const double ul = ou[r], wl = owr[r], vl = ov[r];
-          a[r][0] -= ul * wr[0] + wl * u[0];
-          s0 = fma(a[r][0], vl, s0);
-          if (two) {
-            a[r][1] -= ul * wr[1] + wl * u[1];
-            s1 = fma(a[r][1], vl, s1);
+        for (int r = 0; r < GR; ++r) {
+          ul_[r] = ow[GR * g + r];
+          wl_[r] = ow[RW + GR * g + r];
+          vl_[r] = ow[2 * RW + GR * g + r];
+        }
+      };
+      if constexpr (!HEAD) own_rows(g0, ul, wl, vl);
+#pragma unroll
+      for (int g = 0; g < RW / GR; ++g) {
+        if (g >= g0 && g < g1) {
+          double un[GR], wn[GR], vn[GR];
+          if constexpr (HEAD) own_rows(g, ul, wl, vl);
+          else own_rows(g + 1 < RW / GR ? g + 1 : g, un, wn, vn);
+#pragma unroll
+          for (int r = 0; r < GR; ++r) {
+            double* const ar = a[GR * g + r];
+            ar[0] = fma(-ul[r], wr[0], fma(-wl[r], u[0], ar[0]));
+            s0 = fma(ar[0], vl[r], s0);
+            if (two) {
+              ar[1] = fma(-ul[r], wr[1], fma(-wl[r], u[1], ar[1]));
+              s1 = fma(ar[1], vl[r], s1);
+            }
+            if (w + TW * (GR * g + r) == j + 1) {  // the next step's row
+              nrow[ln] = ar[0];
+              nrow[64 + ln] = ar[1];
+            }
           }
-          if (l == j + 1) {
-            nrow[ln] = a[r][0];
-            nrow[64 + ln] = a[r][1];
+          if constexpr (!HEAD) {
+#pragma unroll
+            for (int r = 0; r < GR; ++r) {
+              ul[r] = un[r];
+              wl[r] = wn[r];
+              vl[r] = vn[r];
+            }
           }
         }
       }
-      double* pj = pp + ((j & 1) * 8 + w) * EIG_T;
+      double* pj = pp + ((j & 1) * TW + w) * EIG_T;
       pj[ln] = s0;
       if (two) pj[64 + ln] = s1;
+      const double kp = wave_sum(fma(s0, v[0], s1 * v[1]));
+      if (ln == 0) kps[(j & 1) * TW + w] = kp;
     }
     __syncthreads();
-    if (w < 8) {
-      const double* pj = pp + (j & 1) * 8 * EIG_T;
-      double p[2] = {0.0, 0.0};
+    if (w < TW) {
+      const double* pj = pp + (j & 1) * TW * EIG_T;
+      double p[2] = {0.0, 0.0}, kp = 0.0;
 #pragma unroll
-      for (int g = 0; g < 8; ++g) {
+      for (int g = 0; g < TW; ++g) {
         p[0] += pj[g * EIG_T + ln];
         if (two) p[1] += pj[g * EIG_T + 64 + ln];
+        kp += kps[(j & 1) * TW + g];
       }
-#pragma unroll
-      for (int c = 0; c < 2; ++c) p[c] = ln + 64 * c > j && ln + 64 * c < L ? p[c] * b : 0.0;
-      const double K = 0.5 * b * wave_sum(fma(p[0], v[0], p[1] * v[1]));
+      // w = p - (b / 2)(v^T p) v with p = b A v
+      const double K = 0.5 * b * b * kp;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        wr[c] = fma(-K, v[c], p[c]);
+        const int i = ln + 64 * c;
+        wr[c] = i > j && i < L ? fma(-K, v[c], p[c] * b) : 0.0;
         u[c] = v[c];
       }
-      double* owr = own + w * 48 + 32;
-      if ((ln & 7) == w) {
-        owr[ln >> 3] = wr[0];
-        owr[8 + (ln >> 3)] = wr[1];
+      double* const ow = own + w * 3 * RW;
+      if (ln % TW == w) {
+        ow[ln / TW] = u[0];
+        ow[RL + ln / TW] = u[1];
+        ow[RW + ln / TW] = wr[0];
+        ow[RW + RL + ln / TW] = wr[1];
       }
       wave_lds_fence();
     }
   }
   // the last two rows, with the pending update of the last step
-  if (w < 8) {
+  if (w < TW) {
     if (w == 0 && L >= 2) {
       const int j = L - 2;
       const double* rb = rowb + (j & 1) * EIG_T;
@@ -584,11 +659,11 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
         bl[o + j] = 0.0;
       }
     }
-    if (w == ((L - 1) & 7)) {
+    if (w == (L - 1) % TW) {
       double x = 0.0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (w + 8 * r == L - 1) x = L - 1 < 64 ? a[r][0] - 2.0 * u[0] * wr[0] : a[r][1] - 2.0 * u[1] * wr[1];
+      for (int r = 0; r < RW; ++r)
+        if (w + TW * r == L - 1) x = L - 1 < 64 ? a[r][0] - 2.0 * u[0] * wr[0] : a[r][1] - 2.0 * u[1] * wr[1];
       x = lane_get(x, (L - 1) & 63);
       if (ln == 0) {
         dl[m - 1] = x;
@@ -607,11 +682,12 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
   const int ex = __builtin_amdgcn_frexp_exp(tn);
   tn = ldexp(tn, -ex);
   __syncthreads();
-  for (int i = t; i < m; i += NTH) {
-    const double e = ldexp(el[i], -ex);
-    dl[i] = ldexp(dl[i], -ex);
+  for (int i = t; i < m + 7; i += NTH) {  // e2l[i] couples rows i - 1 and i
+    const double e = i < m ? ldexp(el[i], -ex) : 0.0;
+    dl[i] = i < m ? ldexp(dl[i], -ex) : 4.0;
     el[i] = e;
-    e2l[i] = fmax(e * e, 1e-60);
+    e2l[i + 1] = fmax(e * e, 1e-34);
+    if (i == 0) e2l[0] = 0.0;
   }
   // the work arrays of the inverse iteration after the packed Householder vectors when they fit there,
   // else the vectors move to A (whose rows hold those of the steps in global memory already)
@@ -627,8 +703,8 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
   __syncthreads();
 
   // ---- eigenvalues: one wave per wanted eigenvalue; in each round its lanes evaluate the Sturm count
-  // at 128 interior points of the current interval, which shrinks 129-fold (counts are monotone in x,
-  // so the crossing is found by ballots)
+  // at 64 interior points of the current interval, which shrinks 65-fold (counts are monotone in x, so
+  // the crossing is found by a ballot)
   {
     double lo = 1e300, hi = -1e300;
     for (int i = ln; i < m; i += 64) {
@@ -642,13 +718,12 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
       double x0 = lo - 1e-14 * tn, x1 = hi + 1e-14 * tn;
       for (int it = 0; it < 40; ++it) {
         if (x1 - x0 <= 2.220446049250313e-16 * fmax(fabs(x0), fabs(x1)) + 1e-300) break;
-        const double h = (x1 - x0) / 129.0;
-        const double xa = x0 + (2 * ln + 1) * h, xb = x0 + (2 * ln + 2) * h;
-        const int2 cnt = sturm_pair(m, dl, e2l, xa, xb);
+        const double h = (x1 - x0) * (1.0 / 65.0);
+        const double x = x0 + (ln + 1) * h;
         // the lowest P points have count <= idx (monotone); the eigenvalue lies between points P and P + 1
-        const int P = __popcll(__ballot(xa < x1 && cnt.x <= idx)) + __popcll(__ballot(xb < x1 && cnt.y <= idx));
+        const int P = __popcll(__ballot(x < x1 && sturm_count(m, dl, e2l, x) <= idx));
         const double na = P > 0 ? x0 + P * h : x0;
-        const double nb = P < 128 ? x0 + (P + 1) * h : x1;
+        const double nb = P < 64 ? x0 + (P + 1) * h : x1;
         if (!(na < nb) || (na == x0 && nb == x1)) break;
         x0 = na;
         x1 = fmin(nb, x1);
@@ -677,7 +752,7 @@ __global__ __launch_bounds__(NTH) void k_sym_eig(int m, int nw, const double* __
       // repeated eigenvalues: separate the shifts slightly so the vectors differ
       int rep = 0;
       for (int c2 = t - 1; c2 >= 0 && lam[t] - lam[c2] < 10.0 * epsp; --c2) ++rep;
-      inverse_iteration(m, nw, dl, el, lam[t] + 10.0 * epsp * rep, epsp, 0x9E3779B9u * (uint32_t)(t + 1), u1 + t,
+      inverse_iteration<HEAD ? 4 : 8>(m, nw, dl, el, lam[t] + 10.0 * epsp * rep, epsp, 0x9E3779B9u * (uint32_t)(t + 1), u1 + t,
                         ll + t, r0 + t, Y + t, piv + t);
     }
     __syncthreads();
