@@ -10,10 +10,12 @@ namespace sppc {
 
 namespace {
 
-// rows per partial sum in gemm_tn: enough chunks to fill the chip, at most 2048 rows each
+// Rows per partial sum in gemm_tn: about 512 chunks, 1024 beyond 2^20 rows, where a pass is long enough
+// for the last wave to matter: with 2048-row chunks n = 1.17M gave 572 workgroups per 64 columns, 2.2 per
+// CU (128 columns, 8 wanted: 268 us, 4.5 TB/s); 1024 chunks are 4 per CU: 248 us, 4.8 TB/s.
 inline int64_t tn_chunk(int64_t n) {
-  int64_t c = (n / 512 + 31) / 32 * 32;
-  return c < 32 ? 32 : (c > 2048 ? 2048 : c);
+  int64_t c = (n / (n > (1 << 20) ? 1024 : 512) + 31) / 32 * 32;
+  return c < 32 ? 32 : c;
 }
 // ---------------------------------------------------------------- MFMA tall-skinny products
 // v_mfma_f64_16x16x4f64 (wave64): lane l supplies A[l%16][l/16] and B[l/16][l%16] of a
