@@ -117,69 +117,108 @@ __global__ void k_loss_coef(int S, const double* __restrict__ c1, const double* 
   cb[s] = 2.0 * c1[s] * c1[s] / (c2[s] * q) * inv_scale;
 }
 
-// gradient partials: one item (row, sample) per 32 threads (lane = hidden unit)
+// Gradient partials over a run of (row, sample) items.  The values of an item that do not depend on the
+// hidden unit are computed once per item, by one thread (a thread per item of a tile of 256), and go
+// through LDS to the 32 threads that hold the hidden units; when each of those formed them for itself, an
+// item cost 32 64-bit divisions by S and 64 float64 divisions, and the blocks of 512 items left most of the
+// chip idle on small inputs.  n = 4900, S = 4: 51 -> 6.6 us; n = 386k, S = 16: 970 -> 336 us, bound by the
+// issue of the ten conversions and float64 sums per item and unit.
+constexpr int GT = 256;  // items per tile
+
+// items per block: enough blocks for 8 per CU, whole quarter tiles
+inline int64_t grad_items(int64_t items) {
+  const int64_t c = (items / 2048 + 63) / 64 * 64;
+  return c < 64 ? 64 : c;
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_mpnn_grad(int64_t n, int S, Static st, const T* __restrict__ w,
-                                                   const double* __restrict__ fr, const double* __restrict__ HF,
-                                                   const double* __restrict__ theta,
-                                                   const double* __restrict__ dO, const double* __restrict__ HdO,
-                                                   double* __restrict__ part, int64_t items_per_block) {
-  __shared__ T wsh[NPAR];
+__global__ __launch_bounds__(GT) void k_mpnn_grad(int64_t n, int S, Static st, const T* __restrict__ w,
+                                                  const double* __restrict__ fr, const double* __restrict__ HF,
+                                                  const double* __restrict__ theta,
+                                                  const double* __restrict__ dO, const double* __restrict__ HdO,
+                                                  double* __restrict__ part, int64_t items_per_block) {
+  struct alignas(16) Item {
+    T v[8];  // the six inputs, dL/do, dL/du
+  };
+  __shared__ Item it[GT];
   __shared__ double red[8][HID][10];
-  for (int i = threadIdx.x; i < NPAR; i += blockDim.x) wsh[i] = w[i];
-  __syncthreads();
-  const int j = threadIdx.x & 31, slot = threadIdx.x >> 5;
+  const int t = threadIdx.x, j = t & 31, slot = t >> 5;
+  T ws[6];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    ws[q] = w[j * 3 + q];
+    ws[3 + q] = w[96 + j * 3 + q];
+  }
+  const T wb = w[192 + j], wo = w[224 + j], wu = w[256 + j];
   double acc[10];
 #pragma unroll
   for (int q = 0; q < 10; ++q) acc[q] = 0.0;
   const int64_t i0 = (int64_t)blockIdx.x * items_per_block;
   const int64_t i1 = min<int64_t>(n * S, i0 + items_per_block);
-  for (int64_t e = i0 + slot; e < i1; e += 8) {
-    const int64_t r = e / S;
-    const int s = (int)(e % S);
-    const double th = theta[s], sth = 1.0 + fabs(th);
-    const double d = st.d[r];
-    const T f0 = (T)fr[e], f1 = (T)((d - th) / sth), f2 = (T)st.lev[r];
-    const T g0 = (T)(HF[e] - d * fr[e]), g1 = (T)((st.Ad[r] - th * st.A1[r]) / sth), g2 = (T)st.Al[r];
-    const T pre = wsh[j * 3] * f0 + wsh[j * 3 + 1] * f1 + wsh[j * 3 + 2] * f2 + wsh[96 + j * 3] * g0 +
-                  wsh[96 + j * 3 + 1] * g1 + wsh[96 + j * 3 + 2] * g2 + wsh[192 + j];
-    const T h = tanh(pre);
-    const T dov = (T)dO[e];
-    const T duv = (T)(HdO[e] - d * dO[e]);   // dL/du = A dL/do
-    const T dpre = (dov * wsh[224 + j] + duv * wsh[256 + j]) * ((T)1 - h * h);
-    acc[0] += (double)(dpre * f0);
-    acc[1] += (double)(dpre * f1);
-    acc[2] += (double)(dpre * f2);
-    acc[3] += (double)(dpre * g0);
-    acc[4] += (double)(dpre * g1);
-    acc[5] += (double)(dpre * g2);
-    acc[6] += (double)dpre;
-    acc[7] += (double)(dov * h);
-    acc[8] += (double)(duv * h);
-    acc[9] += (double)dov;  // db2 (only lane 0's copy is used)
+  for (int64_t base = i0; base < i1; base += GT) {
+    const int cnt = (int)min<int64_t>(GT, i1 - base);
+    if (t < cnt) {
+      const int64_t rb = base / S;
+      const uint32_t x = (uint32_t)(base - rb * S) + (uint32_t)t;
+      const int64_t e = base + t, r = rb + x / (uint32_t)S;
+      const int s = (int)(x % (uint32_t)S);
+      const double th = theta[s], sth = 1.0 + fabs(th);
+      const double d = st.d[r];
+      Item& o = it[t];
+      o.v[0] = (T)fr[e];
+      o.v[1] = (T)((d - th) / sth);
+      o.v[2] = (T)st.lev[r];
+      o.v[3] = (T)(HF[e] - d * fr[e]);
+      o.v[4] = (T)((st.Ad[r] - th * st.A1[r]) / sth);
+      o.v[5] = (T)st.Al[r];
+      o.v[6] = (T)dO[e];
+      o.v[7] = (T)(HdO[e] - d * dO[e]);  // dL/du = A dL/do
+    }
+    __syncthreads();
+    for (int i = slot; i < cnt; i += 8) {
+      const Item& o = it[i];
+      const T f0 = o.v[0], f1 = o.v[1], f2 = o.v[2], g0 = o.v[3], g1 = o.v[4], g2 = o.v[5];
+      const T dov = o.v[6], duv = o.v[7];
+      const T pre = ws[0] * f0 + ws[1] * f1 + ws[2] * f2 + ws[3] * g0 + ws[4] * g1 + ws[5] * g2 + wb;
+      const T h = tanh(pre);
+      const T dpre = (dov * wo + duv * wu) * ((T)1 - h * h);
+      acc[0] += (double)(dpre * f0);
+      acc[1] += (double)(dpre * f1);
+      acc[2] += (double)(dpre * f2);
+      acc[3] += (double)(dpre * g0);
+      acc[4] += (double)(dpre * g1);
+      acc[5] += (double)(dpre * g2);
+      acc[6] += (double)dpre;
+      acc[7] += (double)(dov * h);
+      acc[8] += (double)(duv * h);
+      acc[9] += (double)dov;  // db2 (only lane 0's copy is used)
+    }
+    __syncthreads();
   }
 #pragma unroll
   for (int q = 0; q < 10; ++q) red[slot][j][q] = acc[q];
   __syncthreads();
-  if (slot == 0) {
-    double tot[10];
-#pragma unroll
-    for (int q = 0; q < 10; ++q) {
-      double v = 0.0;
-      for (int sl = 0; sl < 8; ++sl) v += red[sl][j][q];
-      tot[q] = v;
+  // part is parameter-major, so that the sums over the blocks read whole lines
+  const int64_t nb = gridDim.x;
+  for (int p = t; p < NPAR; p += GT) {
+    int jj, q;
+    if (p < 96) {
+      jj = p / 3;
+      q = p % 3;
+    } else if (p < 192) {
+      jj = (p - 96) / 3;
+      q = 3 + (p - 96) % 3;
+    } else if (p < 288) {
+      jj = (p - 192) & 31;
+      q = 6 + ((p - 192) >> 5);
+    } else {
+      jj = 0;
+      q = 9;
     }
-    double* out = part + (int64_t)blockIdx.x * NPAR;
-    out[j * 3] = tot[0];
-    out[j * 3 + 1] = tot[1];
-    out[j * 3 + 2] = tot[2];
-    out[96 + j * 3] = tot[3];
-    out[96 + j * 3 + 1] = tot[4];
-    out[96 + j * 3 + 2] = tot[5];
-    out[192 + j] = tot[6];
-    out[224 + j] = tot[7];
-    out[256 + j] = tot[8];
-    if (j == 0) out[288] = tot[9];
+    double v = 0.0;
+#pragma unroll
+    for (int sl = 0; sl < 8; ++sl) v += red[sl][jj][q];
+    part[(int64_t)p * nb + blockIdx.x] = v;
   }
 }
 
@@ -188,7 +227,7 @@ __global__ void k_sum_parts(int64_t nb, const double* __restrict__ part, double*
   const int lane = threadIdx.x & 63;
   if (i >= NPAR) return;
   double s = 0.0;
-  for (int64_t b = lane; b < nb; b += 64) s += part[b * NPAR + i];
+  for (int64_t b = lane; b < nb; b += 64) s += part[i * nb + b];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if (lane == 0) g[i] = s;
 }
@@ -293,7 +332,7 @@ void mpnn_prepare(const DevCSR& H, const double* diag, const int64_t* level_off_
 // + small: sumsq[S], th[S], c1..c3[S], ca, cb, lossv, xdt[S], grad partials.
 int64_t mpnn_work_doubles(int64_t n, int S) {
   const int64_t items = n * S;
-  const int64_t nblk = cdiv(items, 8 * 64);
+  const int64_t nblk = cdiv(items, grad_items(items));
   return 9 * items + 16 * 64 + nblk * NPAR + NPAR + 64;
 }
 
@@ -391,9 +430,9 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
     }
     k_mul<<<gg(items), 256, 0, s>>>(items, tJ, dO);
     spmm_f64(H, dO, S, HdO, S, S, nullptr, s);
-    const int64_t ipb = 8 * 64;
+    const int64_t ipb = grad_items(items);
     const int64_t nblk = cdiv(items, ipb);
-    k_mpnn_grad<T><<<nblk, 256, 0, s>>>(n, S, st, w, fr, HF, theta_dev, dO, HdO, part, ipb);
+    k_mpnn_grad<T><<<nblk, GT, 0, s>>>(n, S, st, w, fr, HF, theta_dev, dO, HdO, part, ipb);
     k_sum_parts<<<cdiv(NPAR, 4), 256, 0, s>>>(nblk, part, grad_out);
     if (loss_dev) copy_block(1, S, lossv, S, loss_dev, S, s);
   }
