@@ -34,25 +34,28 @@ struct Static {
   const double* Al;   // A lev
 };
 
-// Y[r][s] = X[r][s] / scale[s]
+// Y[r][s] = X[r][s] / scale[s], with Y32 also its float32 copy (the next product's input)
 __global__ void k_scale_cols(int64_t n, int S, const double* __restrict__ X, int64_t ldx,
-                             const double* __restrict__ sumsq, double* __restrict__ Y) {
+                             const double* __restrict__ sumsq, double* __restrict__ Y, float* __restrict__ Y32) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n * S) return;
   const int64_t r = e / S;
   const int s = (int)(e % S);
   double sr = sqrt(sumsq[s] / (double)n);
   if (!(sr > 0.0)) sr = 1.0;
-  Y[e] = X[r * ldx + s] / sr;
+  const double y = X[r * ldx + s] / sr;
+  Y[e] = y;
+  if (Y32) Y32[e] = (float)y;
 }
 
-// layer 1 + the row parts of layer 2: u = wn.h, hs = ws.h   (HF = H fr, the full product)
+// layer 1 + the row parts of layer 2: u = wn.h, hs = ws.h   (HF = H fr, the full product); with u32 also the
+// float32 copy of u
 template <typename T>
 __global__ __launch_bounds__(256) void k_mpnn_layer1(int64_t n, int S, Static st, const T* __restrict__ w,
                                                      const double* __restrict__ fr,
                                                      const double* __restrict__ HF,
                                                      const double* __restrict__ theta, double* __restrict__ u,
-                                                     double* __restrict__ hs) {
+                                                     float* __restrict__ u32, double* __restrict__ hs) {
   __shared__ T wsh[NPAR];
   for (int i = threadIdx.x; i < NPAR; i += blockDim.x) wsh[i] = w[i];
   __syncthreads();
@@ -74,6 +77,7 @@ __global__ __launch_bounds__(256) void k_mpnn_layer1(int64_t n, int S, Static st
     sh += wsh[224 + j] * h;
   }
   u[e] = (double)su;
+  if (u32) u32[e] = (float)su;
   hs[e] = (double)sh;
 }
 
@@ -105,16 +109,83 @@ __global__ void k_comb_cols(int64_t n, int S, const double* __restrict__ a, cons
   Y[r * ldy + s] = a[s] * X[r * ldx + s] + b[s] * Z[r * ldz + s];
 }
 
-// loss pieces -> coefficients of dL/dt~ = ca e + cb t~ ; loss per sample
-__global__ void k_loss_coef(int S, const double* __restrict__ c1, const double* __restrict__ c2,
-                            const double* __restrict__ c3, double* __restrict__ ca, double* __restrict__ cb,
-                            double* __restrict__ lossv, double inv_scale) {
-  const int s = threadIdx.x;
+// t -= x (x.t) with the dots of the columns on the device, and with f also t *= f
+__global__ void k_project_x(int64_t n, int S, const double* __restrict__ xdt, const double* __restrict__ X,
+                            int64_t ldx, double* __restrict__ t, const double* __restrict__ f) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n * S) return;
+  const int64_t r = e / S;
+  const int s = (int)(e % S);
+  const double v = fma(-xdt[s], X[r * ldx + s], t[e]);
+  t[e] = f ? v * f[e] : v;
+}
+
+// Partials over a chunk of rows of t.e, t.t and e.e per sample, one pass over both (three passes of two
+// operands each cost 110 us at n = 386k, S = 16; this one 17 us).  Column q S + s of part: dot q of sample s.
+inline int64_t ld_chunk(int64_t n) {
+  const int64_t c = (n / 1024 + 63) / 64 * 64;
+  return c < 64 ? 64 : c;
+}
+__global__ __launch_bounds__(256) void k_loss_dots(int64_t n, int S, const double* __restrict__ t,
+                                                   const double* __restrict__ E, double* __restrict__ part,
+                                                   int64_t chunk) {
+  __shared__ double sh[3][256];
+  const int i = threadIdx.x;
+  const int B2 = S <= 1 ? 1 : S <= 2 ? 2 : S <= 4 ? 4 : S <= 8 ? 8 : S <= 16 ? 16 : 32;
+  const int tc = i % B2, tr = i / B2, nrt = 256 / B2;
+  const int64_t r0 = (int64_t)blockIdx.x * chunk;
+  const int64_t r1 = min<int64_t>(n, r0 + chunk);
+  double a = 0.0, b = 0.0, c = 0.0;
+  if (tc < S) {
+#pragma unroll 4
+    for (int64_t r = r0 + tr; r < r1; r += nrt) {
+      const double x = t[r * S + tc], y = E[r * S + tc];
+      a = fma(x, y, a);
+      b = fma(x, x, b);
+      c = fma(y, y, c);
+    }
+  }
+  sh[0][i] = a;
+  sh[1][i] = b;
+  sh[2][i] = c;
+  __syncthreads();
+  for (int o = 128; o >= B2; o >>= 1) {
+    if (i < o)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sh[q][i] += sh[q][i + o];
+    __syncthreads();
+  }
+  if (i < S)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part[((int64_t)blockIdx.x * 3 + q) * S + i] = sh[q][i];
+}
+
+// their sums (the threads of a group over the columns, the groups over the chunks, then the groups in
+// order), the loss per sample and the coefficients of dL/dt~ = ca e + cb t~; one workgroup
+__global__ __launch_bounds__(1024) void k_loss_coef(int64_t nch, int S, const double* __restrict__ part,
+                                                    double* __restrict__ ca, double* __restrict__ cb,
+                                                    double* __restrict__ lossv, double inv_scale) {
+  __shared__ double sh[1024], dot[96];
+  const int t = threadIdx.x, W = 3 * S, G = 1024 / W;
+  double v = 0.0;
+  if (t < G * W) {
+#pragma unroll 8
+    for (int64_t c = t / W; c < nch; c += G) v += part[c * W + t % W];
+  }
+  sh[t] = v;
+  __syncthreads();
+  if (t < W) {
+    double d = 0.0;
+    for (int g = 0; g < G; ++g) d += sh[g * W + t];
+    dot[t] = d;
+  }
+  __syncthreads();
+  const int s = t;
   if (s >= S) return;
-  const double q = c2[s] * c3[s];
-  lossv[s] = 1.0 - c1[s] * c1[s] / q;
-  ca[s] = -2.0 * c1[s] / q * inv_scale;
-  cb[s] = 2.0 * c1[s] * c1[s] / (c2[s] * q) * inv_scale;
+  const double c1 = dot[s], c2 = dot[S + s], q = c2 * dot[2 * S + s];
+  if (lossv) lossv[s] = 1.0 - c1 * c1 / q;
+  ca[s] = -2.0 * c1 / q * inv_scale;
+  cb[s] = 2.0 * c1 * c1 / (c2 * q) * inv_scale;
 }
 
 // Gradient partials over a run of (row, sample) items.  The values of an item that do not depend on the
@@ -296,16 +367,6 @@ __global__ void k_levels(int64_t n, int L, int nsmall, const int64_t* __restrict
   lev[r] = 0.5 * (double)(rel < 0 ? 0 : rel > 2 ? 2 : rel);
 }
 
-__global__ void k_fill_const(int S, double v, double* __restrict__ out) {
-  const int i = threadIdx.x;
-  if (i < S) out[i] = v;
-}
-
-__global__ void k_neg(int S, const double* __restrict__ in, double* __restrict__ out) {
-  const int i = threadIdx.x;
-  if (i < S) out[i] = -in[i];
-}
-
 __global__ void k_mul(int64_t cnt, const double* __restrict__ a, double* __restrict__ b) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < cnt) b[e] *= a[e];
@@ -329,7 +390,7 @@ void mpnn_prepare(const DevCSR& H, const double* diag, const int64_t* level_off_
 }
 
 // Workspace layout (n x S doubles each): fr | HF | u | hs | Hu | t | tJ | dO | HdO  (9 n S)
-// + small: sumsq[S], th[S], c1..c3[S], ca, cb, lossv, xdt[S], grad partials.
+// + small: sumsq, ca, cb, xdt [S], partial sums.
 int64_t mpnn_work_doubles(int64_t n, int S) {
   const int64_t items = n * S;
   const int64_t nblk = cdiv(items, grad_items(items));
@@ -371,70 +432,60 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
   double* HdO = dO + items;
   double* sm = HdO + items;
   double* sumsq = sm;
-  double* c1 = sm + 64;
-  double* c2 = sm + 128;
-  double* c3 = sm + 192;
-  double* ca = sm + 256;
-  double* cb = sm + 320;
-  double* lossv = sm + 384;
-  double* xdt = sm + 448;
-  double* one = sm + 512;
-  double* mxdt = sm + 576;
+  double* ca = sm + 64;
+  double* cb = sm + 128;
+  double* xdt = sm + 192;
   double* part = sm + 16 * 64;
   Static st{diag, lev, Ad, A1, Al};
+  // t~ is built in the caller's output where that does not overlap an operand that is still to be read
+  auto apart = [&](const double* p, int64_t ld, int64_t cols) {
+    const uintptr_t a0 = (uintptr_t)T_out, a1 = (uintptr_t)(T_out + items);
+    return !p || (uintptr_t)(p + ((n - 1) * ld + cols)) <= a0 || (uintptr_t)p >= a1;
+  };
+  if (T_out && apart(R, ldr, S) && apart(X, ldx, S) && apart(E, S, S) && (!basis || apart(basis->Q, basis->ldq, basis->m)))
+    t = T_out;
   // the two aggregations: with the bfloat16 weights (T = float) their products take float32 X when
   // float32 values are stored (float32 products, float64 sums; the network's inputs need no more),
   // the float32 copy of X in tJ's space, which k_mpnn_out fills only after both
+  float* x32 = sizeof(T) == 4 && H.val32 ? (float*)tJ : nullptr;
   auto hprod = [&](const double* Xd, double* Yd) {
-    if constexpr (sizeof(T) == 4) {
-      if (H.val32) {
-        float* x32 = (float*)tJ;
-        copy_to_f32(n, S, Xd, S, x32, S, s);
-        spmm_f32(H, x32, S, Yd, S, S, nullptr, s);
-        return;
-      }
-    }
-    spmm_f64(H, Xd, S, Yd, S, S, nullptr, s);
+    if (x32) spmm_f32(H, x32, S, Yd, S, S, nullptr, s);
+    else spmm_f64(H, Xd, S, Yd, S, S, nullptr, s);
   };
   colsumsq(n, S, R, ldr, sumsq, part, s);
-  k_scale_cols<<<gg(items), 256, 0, s>>>(n, S, R, ldr, sumsq, fr);
+  k_scale_cols<<<gg(items), 256, 0, s>>>(n, S, R, ldr, sumsq, fr, x32);
   hprod(fr, HF);
-  k_mpnn_layer1<T><<<gg(items), 256, 0, s>>>(n, S, st, w, fr, HF, theta_dev, u, hs);
+  k_mpnn_layer1<T><<<gg(items), 256, 0, s>>>(n, S, st, w, fr, HF, theta_dev, u, x32, hs);
   hprod(u, Hu);
   k_mpnn_out<T><<<gg(items), 256, 0, s>>>(n, S, diag, w, R, ldr, theta_dev, hs, u, Hu, t, tJ);
   // t~ = t - x (x.t), or t - Q (Q^T t) with a basis
-  k_fill_const<<<1, 64, 0, s>>>(S, 1.0, one);
   if (!project) {
     // unprojected t = tJ (1 + o) (the step of a single-vector refinement)
   } else if (basis) {
     project_basis(n, S, *basis, t, s);
   } else {
     coldots(n, S, X, ldx, t, S, xdt, part, s);
-    k_neg<<<1, 64, 0, s>>>(S, xdt, mxdt);
-    k_comb_cols<<<gg(items), 256, 0, s>>>(n, S, one, t, S, mxdt, X, ldx, t, S);
+    k_project_x<<<gg(items), 256, 0, s>>>(n, S, xdt, X, ldx, t, nullptr);
   }
-  if (T_out) copy_block(n, S, t, S, T_out, S, s);
+  if (T_out && t != T_out) copy_block(n, S, t, S, T_out, S, s);
   if (E) {
-    coldots(n, S, t, S, E, S, c1, part, s);
-    coldots(n, S, t, S, t, S, c2, part, s);
-    coldots(n, S, E, S, E, S, c3, part, s);
-    k_loss_coef<<<1, 64, 0, s>>>(S, c1, c2, c3, ca, cb, lossv, 1.0 / S);
+    const int64_t lch = ld_chunk(n), lnc = cdiv(n, lch);
+    k_loss_dots<<<lnc, 256, 0, s>>>(n, S, t, E, part, lch);
+    k_loss_coef<<<1, 1024, 0, s>>>(lnc, S, part, ca, cb, loss_dev, 1.0 / S);
     // dL/dt~ = ca e + cb t~ -> dO ; then through the projection and t = tJ (1 + o)
     k_comb_cols<<<gg(items), 256, 0, s>>>(n, S, ca, E, S, cb, t, S, dO, S);
     if (basis) {
       project_basis(n, S, *basis, dO, s);
+      k_mul<<<gg(items), 256, 0, s>>>(items, tJ, dO);
     } else {
       coldots(n, S, X, ldx, dO, S, xdt, part, s);
-      k_neg<<<1, 64, 0, s>>>(S, xdt, mxdt);
-      k_comb_cols<<<gg(items), 256, 0, s>>>(n, S, one, dO, S, mxdt, X, ldx, dO, S);
+      k_project_x<<<gg(items), 256, 0, s>>>(n, S, xdt, X, ldx, dO, tJ);
     }
-    k_mul<<<gg(items), 256, 0, s>>>(items, tJ, dO);
     spmm_f64(H, dO, S, HdO, S, S, nullptr, s);
     const int64_t ipb = grad_items(items);
     const int64_t nblk = cdiv(items, ipb);
     k_mpnn_grad<T><<<nblk, GT, 0, s>>>(n, S, st, w, fr, HF, theta_dev, dO, HdO, part, ipb);
     k_sum_parts<<<cdiv(NPAR, 4), 256, 0, s>>>(nblk, part, grad_out);
-    if (loss_dev) copy_block(1, S, lossv, S, loss_dev, S, s);
   }
   SPPC_LAUNCH_CHECK();
 }
