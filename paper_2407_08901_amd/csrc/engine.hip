@@ -29,6 +29,7 @@ namespace sppc {
 
 constexpr int KB = 32;   // widest block handled by one product / orthonormalisation
 constexpr int NWMAX = 64;
+constexpr int PIN_MP = 512;  // pinned doubles of a network evaluation: theta | loss | gradient | weights
 
 // Device arrays of a context (or, with temp, of one setup phase).  A counting arena allocates
 // nothing: it adds up the workspace bytes its requests would take (the size query runs the same
@@ -1015,7 +1016,7 @@ void setup_impl(sppc_ctx* c, const sppc_csr* Hin, const int64_t* loff, int L, in
   alloc_buffers(c, A);
   const int64_t n0 = c->n0;
   cg_prepare(c->H0, n0, c->cg_rowb, c->cgpart, s);
-  SPPC_HIP(pinned_alloc((void**)&c->pin, sizeof(double) * 4 * NWMAX));
+  SPPC_HIP(pinned_alloc((void**)&c->pin, sizeof(double) * (4 * NWMAX + PIN_MP)));
   SPPC_HIP(pinned_alloc((void**)&c->pin_i, sizeof(int) * 128));
   c->tm.s = s;
 
@@ -1748,24 +1749,27 @@ sppc_status sppc_mpnn_eval(sppc_ctx* c, const float* w_host, int S, const double
     hipStream_t s = c->s;
     MpnnBasis B;
     const MpnnBasis* bp = mpnn_basis(c, Q_dev, m, B);
-    SPPC_HIP(hipMemcpy(c->mp_w, w_host, sizeof(float) * SPPC_MPNN_NPARAM, hipMemcpyHostToDevice));
-    upload_theta(c, theta_host, S);
-    double* grad = grad_host ? c->mp_grad : nullptr;
-    double* lossd = loss_host ? c->mp_loss : nullptr;
-    const double* E = (grad || lossd) ? E_dev : nullptr;
-    if (f64) {
-      std::vector<double> wd(w_host, w_host + SPPC_MPNN_NPARAM);
-      SPPC_HIP(hipMemcpy(c->mp_wd, wd.data(), sizeof(double) * SPPC_MPNN_NPARAM, hipMemcpyHostToDevice));
+    // The host values go through pinned memory that the kernels read and write, with one
+    // synchronisation at the end, which also frees the pinned memory for the next call.  Operands
+    // that the default stream still writes are waited for when the context is on another stream.
+    if (s) SPPC_HIP(hipStreamSynchronize(nullptr));
+    double* th = c->pin + 4 * NWMAX;
+    double *loss = th + 32, *grad = th + 64;
+    float* wf = (float*)(th + 64 + 296);
+    static_assert(64 + 296 + (SPPC_MPNN_NPARAM + 1) / 2 <= PIN_MP && SPPC_MPNN_NPARAM <= 296, "pinned memory");
+    std::copy(theta_host, theta_host + S, th);
+    std::copy(w_host, w_host + SPPC_MPNN_NPARAM, wf);
+    mpnn_inputs(S, wf, th, c->mp_wq, f64 ? c->mp_wd : nullptr, c->mp_th, s);
+    const double* E = (grad_host || loss_host) ? E_dev : nullptr;
+    if (f64)
       mpnn_run<double>(c->H, c->diag, c->mp_lev, c->mp_Ad, c->mp_A1, c->mp_Al, c->mp_wd, S, R_dev, S, X_dev, S,
-                       c->mp_th, E, T_dev, c->mp_grad, c->mp_loss, c->mp_work, bp, s);
-    } else {
-      mpnn_round_bf16(SPPC_MPNN_NPARAM, c->mp_w, c->mp_wq, nullptr, s);
+                       c->mp_th, E, T_dev, grad, loss, c->mp_work, bp, s);
+    else
       mpnn_run<float>(c->H, c->diag, c->mp_lev, c->mp_Ad, c->mp_A1, c->mp_Al, c->mp_wq, S, R_dev, S, X_dev, S,
-                      c->mp_th, E, T_dev, c->mp_grad, c->mp_loss, c->mp_work, bp, s);
-    }
+                      c->mp_th, E, T_dev, grad, loss, c->mp_work, bp, s);
     sync(c);
-    if (loss_host) SPPC_HIP(hipMemcpy(loss_host, c->mp_loss, sizeof(double) * S, hipMemcpyDeviceToHost));
-    if (grad_host) SPPC_HIP(hipMemcpy(grad_host, c->mp_grad, sizeof(double) * SPPC_MPNN_NPARAM, hipMemcpyDeviceToHost));
+    if (loss_host) std::copy(loss, loss + S, loss_host);
+    if (grad_host) std::copy(grad, grad + SPPC_MPNN_NPARAM, grad_host);
     return SPPC_OK;
   });
 }

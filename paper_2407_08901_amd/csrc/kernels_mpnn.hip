@@ -335,6 +335,26 @@ __global__ void k_round_bf16(int cnt, const float* __restrict__ w, float* __rest
   if (wd) wd[i] = (double)q;
 }
 
+// Weights and theta of one evaluation from the caller's pinned host copy (1.2 KB: two copies and their
+// synchronisations cost more than reading it over the link), the weights rounded to bfloat16 (T = float).
+template <typename T>
+__global__ __launch_bounds__(320) void k_mpnn_inputs(int S, const float* __restrict__ w_host,
+                                                     const double* __restrict__ th_host, T* __restrict__ w,
+                                                     double* __restrict__ th) {
+  const int i = threadIdx.x;
+  if (i < NPAR) {
+    if constexpr (sizeof(T) == 4) {
+      uint32_t bits = __float_as_uint(w_host[i]);
+      const uint32_t lsb = (bits >> 16) & 1u;
+      bits += 0x7FFFu + lsb;
+      w[i] = __uint_as_float(bits & 0xFFFF0000u);
+    } else {
+      w[i] = (double)w_host[i];
+    }
+  }
+  if (i < S) th[i] = th_host[i];
+}
+
 // static inputs: lev, and the row sums A d, A 1, A lev from full products
 __global__ void k_static(int64_t n, const double* __restrict__ d, const double* __restrict__ lev,
                          const double* __restrict__ P, double* __restrict__ Ad, double* __restrict__ A1,
@@ -501,6 +521,13 @@ template void mpnn_run<double>(const DevCSR&, const double*, const double*, cons
 
 void mpnn_adam(float* w, float* m, float* v, const double* g, float lr, int step, float* wq, hipStream_t s) {
   k_adam<<<cdiv(NPAR, 256), 256, 0, s>>>(w, m, v, g, lr, 0.9f, 0.999f, 1e-8f, step, wq);
+  SPPC_LAUNCH_CHECK();
+}
+
+void mpnn_inputs(int S, const float* w_host, const double* th_host, float* w32, double* w64, double* th,
+                 hipStream_t s) {
+  if (w64) k_mpnn_inputs<double><<<1, 320, 0, s>>>(S, w_host, th_host, w64, th);
+  else k_mpnn_inputs<float><<<1, 320, 0, s>>>(S, w_host, th_host, w32, th);
   SPPC_LAUNCH_CHECK();
 }
 
