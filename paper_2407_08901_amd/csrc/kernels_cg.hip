@@ -213,20 +213,16 @@ __device__ inline void cg_runs(int win, int ne, int g, int c, bool cok, int mr, 
 }
 
 template <int B, typename VT, bool INIT, bool PIPE>
-__global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
+__global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j, int* hflag) {
   const int t = threadIdx.x;
   const int k = a.k;
   const int par = INIT ? 1 : (j & 1);
-  const double* __restrict__ partin = a.part[par ^ 1];
-  __shared__ double red[NT];
+  constexpr int NW = NT / 64, W2 = 2 * CG_MAXK;
+  __shared__ double red[NW * W2];
   __shared__ double al[CG_MAXK], be[CG_MAXK];
   __shared__ double acc_s[RCH * CG_MAXK];
   __shared__ int soff[RCH + 1];
   __shared__ int nact_s;
-  if (!INIT && j > 0 && a.sc->nact[par ^ 1] == 0) {
-    if (blockIdx.x == 0 && t == 0) a.sc->nact[par] = 0;
-    return;
-  }
   const int lane = t & 63, wv = t >> 6;
   const int g = lane / B, c = lane % B;
   const bool cok = c < k;
@@ -244,102 +240,107 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
   constexpr int OS = NT / CG_MAXK;
   static_assert(2 * OS == RCH, "two row slots per thread and chunk");
   double sg = 0.0, sd = 0.0;
-  double alpha = 0.0, beta = 0.0, oal = 0.0, obe = 0.0;
-  const double osh = oc < k ? a.shift[oc] : 0.0;
+  // What the scalars of this iteration are made of is requested together with the row bounds.
+  double sacc = 0.0, gold = 0.0, aold = 0.0, bb0 = 0.0;
+  int actold = 0, nactold = 1;
+  if (!INIT) {
+    const double* __restrict__ partin = a.part[par ^ 1];
+    constexpr int NPART = NB * W2 / NT;
+    double pin[NPART];
+#pragma unroll
+    for (int u = 0; u < NPART; ++u) pin[u] = partin[(int64_t)(t / W2 + u * (NT / W2)) * W2 + t % W2];
+    if (j > 0) {
+      nactold = a.sc->nact[par ^ 1];
+      if (t < k) {
+        gold = a.sc->gam[par ^ 1][t];
+        aold = a.sc->alp[par ^ 1][t];
+        actold = a.sc->act[par ^ 1][t];
+        bb0 = a.sc->bb[t];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NPART; ++u) sacc += pin[u];
+  }
   const int64_t rb0 = a.rowb[blockIdx.x], rb1 = a.rowb[blockIdx.x + 1];
+  if (!INIT) {
+    if (nactold == 0) {
+      if (blockIdx.x == 0 && t == 0) {
+        a.sc->nact[par] = 0;
+        if (hflag) __hip_atomic_store(hflag, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+      return;
+    }
+    // (r.r, w.r) of iteration j from the NB partials of the previous kernel, in a fixed order:
+    // lane sums over blocks, the two half-waves, then (below) the 16 waves in turn
+    sacc += __shfl_xor(sacc, 32);
+    if (lane < W2) red[wv * W2 + t % W2] = sacc;
+  }
+  // the scalars by the threads below k, after a barrier behind the stores to red
+  auto scalars = [&]() {
+    if (t >= k) return;
+    double gg = 0.0, d = 0.0;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+      gg += red[w2 * W2 + t];
+      d += red[w2 * W2 + CG_MAXK + t];
+    }
+    double al_ = 0.0, be_ = 0.0, gkeep;
+    int now;
+    if (j == 0) {
+      now = gg > 0.0 && d != 0.0;
+      al_ = now ? gg / d : 0.0;
+      gkeep = gg;
+      if (blockIdx.x == 0) a.sc->bb[t] = gg;
+    } else {
+      now = actold && gg > a.tol2 * bb0;
+      if (now) {
+        be_ = gg / gold;
+        const double den = d - be_ * gg / aold;
+        al_ = den != 0.0 ? gg / den : 0.0;
+        if (den == 0.0) {
+          now = 0;
+          be_ = 0.0;
+        }
+      }
+      gkeep = now ? gg : gold;
+    }
+    al[t] = al_;
+    be[t] = be_;
+    const int na = __popcll(__ballot(now));  // over the threads below k, all in the first wave
+    if (blockIdx.x == 0) {
+      a.sc->gam[par][t] = gkeep;
+      a.sc->alp[par][t] = now ? al_ : 0.0;
+      a.sc->act[par][t] = now;
+    }
+    if (t == 0) {
+      nact_s = na;
+      if (blockIdx.x == 0) {
+        a.sc->nact[par] = na;
+        if (hflag) __hip_atomic_store(hflag, na, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (j == 0) a.sc->iters = 0;
+        if (na) a.sc->iters += 1;
+      }
+    }
+  };
   bool first = true;
   for (int64_t c0 = rb0; c0 < rb1 || (first && !INIT); c0 += RCH) {
     const int nr = (int)max<int64_t>(0, min<int64_t>(RCH, rb1 - c0));
-    // operands that do not depend on this iteration's scalars are requested first
     const int64_t e0 = nr > 0 ? a.rp[c0] : 0;
-    const int rpv = (t <= nr && nr > 0) ? (int)(a.rp[c0 + t] - e0) : 0;
-    double orj[2] = {0.0, 0.0}, owj[2] = {0.0, 0.0}, osm[2] = {0.0, 0.0};
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int rl = os + OS * u;
-      if (oc < k && rl < nr) {
-        const int64_t og = (c0 + rl) * k3 + oc;
-        orj[u] = rj[og];
-        if (!INIT) {
-          owj[u] = wj[og];
-          osm[u] = sm[og];
-        }
-      }
-    }
-    if (!INIT && first) {
-      // (r.r, w.r) of iteration j from the NB partials of the previous kernel, in a fixed order:
-      // lane sums over blocks, the two half-waves, then the 16 waves in turn
-      const int v = t % (2 * CG_MAXK);
-      double sacc = 0.0;
-      for (int b2 = t / (2 * CG_MAXK); b2 < NB; b2 += NT / (2 * CG_MAXK))
-        sacc += partin[(int64_t)b2 * 2 * CG_MAXK + v];
-      sacc += __shfl_xor(sacc, 32);
-      if ((t & 63) < 2 * CG_MAXK) red[(t >> 6) * 2 * CG_MAXK + v] = sacc;
-      __syncthreads();
-      if (t < 2 * CG_MAXK) {
-        double tot = 0.0;
-        for (int w2 = 0; w2 < NT / 64; ++w2) tot += red[w2 * 2 * CG_MAXK + t];
-        red[NT - 2 * CG_MAXK + t] = tot;
-      }
-      __syncthreads();
-      if (t < 2 * CG_MAXK) red[t] = red[NT - 2 * CG_MAXK + t];
-      __syncthreads();
-      if (t < k) {
-        const double gg = red[t], d = red[CG_MAXK + t];
-        double al_ = 0.0, be_ = 0.0, gkeep;
-        int now;
-        if (j == 0) {
-          now = gg > 0.0 && d != 0.0;
-          al_ = now ? gg / d : 0.0;
-          gkeep = gg;
-          if (blockIdx.x == 0) a.sc->bb[t] = gg;
-        } else {
-          const double gold = a.sc->gam[par ^ 1][t];
-          const double aold = a.sc->alp[par ^ 1][t];
-          now = a.sc->act[par ^ 1][t] && gg > a.tol2 * a.sc->bb[t];
-          if (now) {
-            be_ = gg / gold;
-            const double den = d - be_ * gg / aold;
-            al_ = den != 0.0 ? gg / den : 0.0;
-            if (den == 0.0) {
-              now = 0;
-              be_ = 0.0;
-            }
-          }
-          gkeep = now ? gg : gold;
-        }
-        al[t] = al_;
-        be[t] = be_;
-        if (blockIdx.x == 0) {
-          a.sc->gam[par][t] = gkeep;
-          a.sc->alp[par][t] = now ? al_ : 0.0;
-          a.sc->act[par][t] = now;
-        }
-        red[t] = now;
-      }
-      __syncthreads();
-      if (t == 0) {
-        int na = 0;
-        for (int cc = 0; cc < k; ++cc) na += red[cc] != 0.0;
-        nact_s = na;
-        if (blockIdx.x == 0) {
-          a.sc->nact[par] = na;
-          if (j == 0) a.sc->iters = 0;
-          if (na) a.sc->iters += 1;
-        }
-      }
-      __syncthreads();
-      if (nact_s == 0) return;
-      alpha = cok ? al[c] : 0.0;
-      beta = cok ? be[c] : 0.0;
-      oal = oc < k ? al[oc] : 0.0;
-      obe = oc < k ? be[oc] : 0.0;
-    }
-    first = false;
-    if (nr == 0) break;
-    if (t <= nr) soff[t] = rpv;
+    if (t <= nr) soff[t] = nr > 0 ? (int)(a.rp[c0 + t] - e0) : 0;
     for (int i = t; i < RCH * CG_MAXK; i += NT) acc_s[i] = 0.0;
     __syncthreads();
+    double alpha = 0.0, beta = 0.0;  // of this lane's column, in the classical form only
+    if (!INIT && first) {
+      scalars();
+      if (!PIPE) {
+        __syncthreads();
+        if (nact_s == 0) return;
+      }
+    }
+    if (!INIT && !PIPE && cok) {
+      alpha = al[c];
+      beta = be[c];
+    }
     const int ne = soff[nr];
     // two windows per trip (one for 16-lane groups): their gathers are in flight together
     constexpr int WT = B <= 8 ? 2 : 1;
@@ -371,8 +372,27 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
       cg_runs<B, VT>(win, ne, g, c, cok, mr1, mv1, xv1, acc_s);
       cg_runs<B, VT>(win2, ne, g, c, cok, mr2, mv2, xv2, acc_s);
     }
+    // this thread's rows, requested before the barrier that completes the product
+    double orj[2] = {0.0, 0.0}, owj[2] = {0.0, 0.0}, osm[2] = {0.0, 0.0};
+    double ox[2] = {0.0, 0.0}, op[2] = {0.0, 0.0}, oz[2] = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int rl = os + OS * u;
+      if (oc >= k || rl >= nr) continue;
+      const int64_t o = (c0 + rl) * k + oc, og = (c0 + rl) * k3 + oc;
+      orj[u] = rj[og];
+      if (INIT) continue;
+      owj[u] = wj[og];
+      osm[u] = sm[og];
+      ox[u] = a.x[o];
+      op[u] = a.p[o];
+      if (PIPE) oz[u] = a.z[o];
+    }
     __syncthreads();
+    if (!INIT && PIPE && first && nact_s == 0) return;
+    first = false;
     if (oc < k) {
+      const double oal = INIT ? 0.0 : al[oc], obe = INIT ? 0.0 : be[oc], osh = a.shift[oc];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int rl = os + OS * u;
@@ -384,11 +404,11 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
             rnew = orj[u];
             wv2 = acc_s[rl * CG_MAXK + oc] - osh * rnew;
           } else if (!PIPE) {
-            const double pv = orj[u] + obe * a.p[o];
+            const double pv = orj[u] + obe * op[u];
             const double sv = owj[u] + obe * osm[u];
             a.p[o] = pv;
             sj[og] = sv;
-            a.x[o] = fma(oal, pv, a.x[o]);
+            a.x[o] = fma(oal, pv, ox[u]);
             rnew = orj[u] - oal * sv;
             rn[og] = rnew;
             wv2 = acc_s[rl * CG_MAXK + oc] - osh * rnew;
@@ -396,13 +416,13 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
             // pipelined CG: q = A w_j, z = q + beta z, s = w + beta s, p = r + beta p,
             // x += alpha p, r -= alpha s, w -= alpha z
             const double q = acc_s[rl * CG_MAXK + oc] - osh * owj[u];
-            const double zv = q + obe * a.z[o];
+            const double zv = q + obe * oz[u];
             const double sv = owj[u] + obe * osm[u];
-            const double pv = orj[u] + obe * a.p[o];
+            const double pv = orj[u] + obe * op[u];
             a.z[o] = zv;
             a.p[o] = pv;
             sj[og] = sv;
-            a.x[o] = fma(oal, pv, a.x[o]);
+            a.x[o] = fma(oal, pv, ox[u]);
             rnew = orj[u] - oal * sv;
             rn[og] = rnew;
             wv2 = owj[u] - oal * zv;
@@ -414,21 +434,23 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j) {
       }
     }
     __syncthreads();
+    if (nr == 0) break;
   }
   // block partials in a fixed order: the four lanes of a column within a wave, then the waves
   sg += __shfl_xor(sg, 16);
   sg += __shfl_xor(sg, 32);
   sd += __shfl_xor(sd, 16);
   sd += __shfl_xor(sd, 32);
-  if ((t & 63) < CG_MAXK) {
-    red[(t >> 6) * 2 * CG_MAXK + oc] = sg;
-    red[(t >> 6) * 2 * CG_MAXK + CG_MAXK + oc] = sd;
+  if (lane < CG_MAXK) {
+    red[wv * W2 + oc] = sg;
+    red[wv * W2 + CG_MAXK + oc] = sd;
   }
   __syncthreads();
-  if (t < 2 * CG_MAXK) {
+  if (t < W2) {
     double tot = 0.0;
-    for (int w2 = 0; w2 < NT / 64; ++w2) tot += red[w2 * 2 * CG_MAXK + t];
-    a.part[par][(int64_t)blockIdx.x * 2 * CG_MAXK + t] = tot;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) tot += red[w2 * W2 + t];
+    a.part[par][(int64_t)blockIdx.x * W2 + t] = tot;
   }
 }
 
@@ -676,29 +698,30 @@ int cg_solve(const DevCSR& H0, int64_t n0, int k, int D, const double* shift, co
   // the pipelined form (one gathered vector per entry) for loose tolerances; its recursively
   // updated residual drifts from the true one, so tight tolerances keep the classical form
   const bool pipe = tol >= 1e-9;
-#define SPPC_CG_LAUNCH(BB, INIT, J)                                                \
+#define SPPC_CG_LAUNCH(BB, INIT, J, HF)                                                \
   if (INIT) {                                                                       \
-    if (f64) k_cg_iter<BB, double, true, false><<<NB, NT, 0, s>>>(a, J);            \
-    else k_cg_iter<BB, float, true, false><<<NB, NT, 0, s>>>(a, J);                 \
+    if (f64) k_cg_iter<BB, double, true, false><<<NB, NT, 0, s>>>(a, J, HF);            \
+    else k_cg_iter<BB, float, true, false><<<NB, NT, 0, s>>>(a, J, HF);                 \
   } else if (pipe) {                                                                \
-    if (f64) k_cg_iter<BB, double, false, true><<<NB, NT, 0, s>>>(a, J);            \
-    else k_cg_iter<BB, float, false, true><<<NB, NT, 0, s>>>(a, J);                 \
+    if (f64) k_cg_iter<BB, double, false, true><<<NB, NT, 0, s>>>(a, J, HF);            \
+    else k_cg_iter<BB, float, false, true><<<NB, NT, 0, s>>>(a, J, HF);                 \
   } else {                                                                          \
-    if (f64) k_cg_iter<BB, double, false, false><<<NB, NT, 0, s>>>(a, J);           \
-    else k_cg_iter<BB, float, false, false><<<NB, NT, 0, s>>>(a, J);                \
+    if (f64) k_cg_iter<BB, double, false, false><<<NB, NT, 0, s>>>(a, J, HF);           \
+    else k_cg_iter<BB, float, false, false><<<NB, NT, 0, s>>>(a, J, HF);                \
   }
-#define SPPC_CG_STEP(INIT, J)      \
+#define SPPC_CG_STEP(INIT, J, HF)  \
   if (k <= 4) {                    \
-    SPPC_CG_LAUNCH(4, INIT, J)     \
+    SPPC_CG_LAUNCH(4, INIT, J, HF)     \
   } else if (k <= 8) {             \
-    SPPC_CG_LAUNCH(8, INIT, J)     \
+    SPPC_CG_LAUNCH(8, INIT, J, HF)     \
   } else {                         \
-    SPPC_CG_LAUNCH(16, INIT, J)    \
+    SPPC_CG_LAUNCH(16, INIT, J, HF)    \
   }
-  SPPC_CG_STEP(true, 0)
-  // The active count is read back after every 16 iterations without draining the stream: the
-  // host waits for the count of the batch before the one just queued, so the GPU always has a
-  // batch to run.  Iterations queued after convergence return at once.
+  SPPC_CG_STEP(true, 0, nullptr)
+  // The last iteration of a batch of 8 writes its active count to pinned host memory.  The host waits
+  // for the batch before the one just queued, so the GPU always has a batch to run.  Iterations
+  // queued after convergence return at once, 4-5 us each (batches of 16, read back by a copy, left 24
+  // of them per solve on average).
   hipEvent_t ev[2] = {nullptr, nullptr};
   auto cleanup = [&]() {
     for (hipEvent_t e : ev)
@@ -709,14 +732,15 @@ int cg_solve(const DevCSR& H0, int64_t n0, int k, int D, const double* shift, co
     SPPC_HIP(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
     int batch = 0;
     for (int j = 0; j < maxit; ++j) {
-      SPPC_CG_STEP(false, j)
-      if ((j + 1) % 16 == 0 || j + 1 == maxit) {
+      const bool last = (j + 1) % 8 == 0 || j + 1 == maxit;
+      int* const hf = last ? host_flag + (batch & 1) : nullptr;
+      SPPC_CG_STEP(false, j, hf)
+      if (last) {
         SPPC_LAUNCH_CHECK();
-        SPPC_HIP(hipMemcpyAsync(host_flag + (batch & 1), &sc->nact[j & 1], sizeof(int), hipMemcpyDeviceToHost, s));
         SPPC_HIP(hipEventRecord(ev[batch & 1], s));
         if (batch > 0) {
           SPPC_HIP(hipEventSynchronize(ev[(batch - 1) & 1]));
-          if (host_flag[(batch - 1) & 1] == 0) break;
+          if (((volatile int*)host_flag)[(batch - 1) & 1] == 0) break;
         }
         ++batch;
       }
