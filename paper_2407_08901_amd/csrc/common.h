@@ -79,6 +79,7 @@ struct PanelH {
   int RB = 0;                 // rows per block
   int P = 0;                  // panels
   int PW = 0;                 // columns per panel (<= 65536)
+  double run = 0.0;           // mean entries of a row in a panel
   int64_t* bstart = nullptr;  // [nblocks + 1]: first entry of each block (multiples of 8)
   int32_t* bcount = nullptr;  // [nblocks]: entries of each block, without the padding
   uint32_t* ent = nullptr;    // column | row-in-block << 24

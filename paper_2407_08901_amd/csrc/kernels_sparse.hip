@@ -532,7 +532,8 @@ __global__ void k_view_fill(int64_t n0, const int64_t* __restrict__ rp, const in
 //
 // Inside a tile, group g of G = B / CPL lanes takes U = 8 entries; lane h of the group gathers
 // columns [h*CPL, h*CPL + CPL) (CPL = min(B, 4)) of each entry's row of X with 16-byte loads and
-// adds the products to the row's LDS accumulators (native float64 LDS adds).  The words and values
+// adds the products, or with RUNS their sums over consecutive entries of one row, to the row's LDS
+// accumulators (native float64 LDS adds, about 18 clocks each per 64 lanes at random rows).  The words and values
 // of the tile D steps ahead are requested after the gathers of the current one, each stream byte by
 // one lane: the lanes of a group load a share of its 8 entries (G = 2, 4) and pass them on by DPP
 // moves, and a lane alone (G = 1) takes two runs of 4 entries so that the 64 lanes read consecutive
@@ -663,7 +664,7 @@ struct PanelTile {
   }
 };
 
-template <int B, int NW, int D, typename VT, typename XT>
+template <int B, int NW, int D, bool RUNS, typename VT, typename XT>
 __global__ __launch_bounds__(NW * 64) void k_spmm_panel(int64_t n, const int64_t* __restrict__ bstart,
                                                     const int32_t* __restrict__ bcount,
                                                     const uint32_t* __restrict__ ent,
@@ -711,16 +712,48 @@ __global__ __launch_bounds__(NW * 64) void k_spmm_panel(int64_t n, const int64_t
       // loads return in issue order: the tile D steps ahead is requested after the gathers
       asm volatile("" ::: "memory");
       tl[d].load(ent, pval, e0 + D * step, s1, h);
+      if constexpr (RUNS) {
+        // consecutive entries of one row are summed in registers, one set of LDS adds per run
+        double run[CPL];
 #pragma unroll
-      for (int q = 0; q < U; ++q) {
-        if (e0 + Tile::at(q) < s1) {
-          double* yr = ysh + (int)(wd[q] >> 24) * YS + h * CPL;
+        for (int j = 0; j < CPL; ++j) run[j] = 0.0;
+        uint32_t cur = wd[0] >> 24;
 #pragma unroll
-          for (int j = 0; j < CPL; ++j) {
-            if constexpr (sizeof(XT) == 4) {
-              atomicAdd(yr + j, (double)(cv[q] * xv[q].v[j]));  // float32 product, float64 sum
-            } else {
-              atomicAdd(yr + j, (double)cv[q] * xv[q].v[j]);
+        for (int q = 0; q < U; ++q) {
+          if (e0 + Tile::at(q) < s1) {
+            if (q > 0 && (wd[q] >> 24) != cur) {
+              double* yr = ysh + (int)cur * YS + h * CPL;
+#pragma unroll
+              for (int j = 0; j < CPL; ++j) {
+                atomicAdd(yr + j, run[j]);
+                run[j] = 0.0;
+              }
+              cur = wd[q] >> 24;
+            }
+#pragma unroll
+            for (int j = 0; j < CPL; ++j) {
+              if constexpr (sizeof(XT) == 4) run[j] += (double)(cv[q] * xv[q].v[j]);
+              else run[j] = fma((double)cv[q], xv[q].v[j], run[j]);
+            }
+          }
+        }
+        if (e0 < s1) {
+          double* yr = ysh + (int)cur * YS + h * CPL;
+#pragma unroll
+          for (int j = 0; j < CPL; ++j) atomicAdd(yr + j, run[j]);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+          if (e0 + Tile::at(q) < s1) {
+            double* yr = ysh + (int)(wd[q] >> 24) * YS + h * CPL;
+#pragma unroll
+            for (int j = 0; j < CPL; ++j) {
+              if constexpr (sizeof(XT) == 4) {
+                atomicAdd(yr + j, (double)(cv[q] * xv[q].v[j]));  // float32 product, float64 sum
+              } else {
+                atomicAdd(yr + j, (double)cv[q] * xv[q].v[j]);
+              }
             }
           }
         }
@@ -762,7 +795,7 @@ __global__ void k_pad_copy(int64_t n, int b, const XT* __restrict__ X, int64_t l
 // same load, so the workgroups progress at the same rate and stay within a few panels of each
 // other (an uneven round lets the workgroups on busier CUs fall behind, and the gathers of
 // X then miss L2).
-template <int B, int NW, int D, typename VT, typename XT>
+template <int B, int NW, int D, bool RUNS, typename VT, typename XT>
 void spmm_panel_rounds(const PanelH& P, const VT* val, const XT* Xc, double* Y, int64_t ldy, int b, int bpc,
                        hipStream_t s, const double* X64, int64_t ldx64) {
   static int cus = 0;
@@ -775,7 +808,7 @@ void spmm_panel_rounds(const PanelH& P, const VT* val, const XT* Xc, double* Y, 
   const int per = cus * bpc;
   for (int r0 = 0; r0 < P.nblocks; r0 += per) {
     const int nb = std::min(per, P.nblocks - r0);
-    k_spmm_panel<B, NW, D, VT, XT><<<nb, NW * 64, 0, s>>>(P.n, P.bstart, P.bcount, P.ent, val, Xc, Y, ldy, b, r0, P.dg,
+    k_spmm_panel<B, NW, D, RUNS, VT, XT><<<nb, NW * 64, 0, s>>>(P.n, P.bstart, P.bcount, P.ent, val, Xc, Y, ldy, b, r0, P.dg,
                                                        X64, ldx64);
   }
   SPPC_LAUNCH_CHECK();
@@ -813,10 +846,32 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
   // (its rows then come from HBM at longer latency, and more rows in flight per CU pay), and for
   // widths up to 8, whose accumulators leave LDS for as many rows in flight.
   const bool big = (int64_t)P.n * 16 * (int64_t)sizeof(XT) > ((int64_t)256 << 20);
+  // Sums over runs of a row's entries where a row has several in a panel (run = their mean): the LDS adds
+  // of the wider products are their bound, and a run costs one set.  Measured (ms, without / with):
+  //   float32 X  b = 8:   run 1.4 1.54 / 1.42, 2.8 1.55 / 1.44 (n = 1.17M), 3.2 1.51 / 1.32 (772k),
+  //                       6.4 0.73 / 0.65 (386k), six one-wave workgroups per CU
+  //              b = 16:  1.95 / 1.85, 1.98 / 1.90, 1.77 / 1.69 with four two-wave workgroups per CU; 0.97 /
+  //                       0.80 with two four-wave ones (1.93 at run 2.8)
+  //   float64 X  b = 8:   1.68 / 1.70, 1.69 / 1.71, 1.64 / 1.61, 0.86 / 0.80
+  //              b = 16:  2.17 / 2.38, 2.19 / 2.41, 2.06 / 2.10, 1.06 / 0.95 (three two-wave workgroups)
+  // Up to b = 4 the sums change nothing (+-5%).  Below one entry per row and panel there are no runs.
+  if constexpr (B >= 8) {
+    if (!big && P.run >= (sizeof(XT) == 4 ? 1.2 : 4.0)) {
+      if constexpr (B == 8)
+        spmm_panel_rounds<B, 1, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 6, s, X64, ldx64);
+      else if constexpr (sizeof(XT) == 8)
+        spmm_panel_rounds<B, 2, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 3, s, X64, ldx64);
+      else if (P.run >= 4.0)
+        spmm_panel_rounds<B, 4, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 2, s, X64, ldx64);
+      else
+        spmm_panel_rounds<B, 2, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
+      return;
+    }
+  }
   if (big || B <= 8)
-    spmm_panel_rounds<B, 1, 2, VT, XT>(P, val, Xc, Y, ldy, b, !big && B == 8 && sizeof(XT) == 4 ? 8 : 4, s, X64, ldx64);
+    spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, !big && B == 8 && sizeof(XT) == 4 ? 8 : 4, s, X64, ldx64);
   else
-    spmm_panel_rounds<B, 2, 2, VT, XT>(P, val, Xc, Y, ldy, b, sizeof(XT) == 4 ? 4 : 2, s, X64, ldx64);
+    spmm_panel_rounds<B, 2, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, sizeof(XT) == 4 ? 4 : 2, s, X64, ldx64);
 }
 
 // Widths above 16 go in column blocks of 16 and the rest, each through the copy of X.
@@ -1286,6 +1341,7 @@ void build_panel(const DevCSR& H, int PW, PanelH& out, hipStream_t s) {
   out.RB = PANEL_RB;
   out.PW = PW;
   out.P = (int)cdiv(n, PW);
+  out.run = (double)H.nnz / ((double)n * out.P);
   out.nblocks = (int)cdiv(n, PANEL_RB);
   int32_t* padded = nullptr;
   int64_t* bsum = nullptr;

@@ -1,5 +1,6 @@
 """The panel product at the widths where its kernel changes: 1, 2 and 4 lanes per entry, one and several
-column blocks, aligned and unaligned X, float32 and float64 values, against SciPy in float64."""
+column blocks, aligned and unaligned X, float32 and float64 values, 12, 2.5 and 0.26 entries per row and
+panel (with and without sums over runs), against SciPy in float64."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +20,7 @@ def P():
 
 @pytest.mark.parametrize("val64", [False, True])
 @pytest.mark.parametrize("xt", [torch.float64, torch.float32])
-@pytest.mark.parametrize("sizes,pw", [((40, 200, 17), 64), ((300, 3000, 20000), 1000)])
+@pytest.mark.parametrize("sizes,pw", [((40, 200, 17), 64), ((300, 3000, 20000), 1000), ((300, 3000, 20000), 100)])
 def test_panel_widths(P, sizes, pw, xt, val64):
     A = levelgen.generate(sizes, 60, 91)   # n = 257: one row beyond a block of 256
     vals = A.val.astype(np.float64)
