@@ -463,6 +463,95 @@ __global__ __launch_bounds__(256) void k_spmm_wide(int64_t n, const int64_t* __r
   }
 }
 
+// The plain product with 16-byte gathers: L lanes take the B = 2 L columns of one nonzero, a wave takes R
+// rows, a window of 64 nonzeros at a time each; the window of the next row (R = 1: the next of this row) is
+// in flight during the gathers.  A full window has no bounds checks, so its gathers are issued together.
+// The product is bound by the L1 misses of the gathers (0.96 ns per row of X and CU from L2) and, where X
+// exceeds the 4 MB L2, by its misses: there fewer waves with more rows each, which stay closer together in
+// the columns, miss less.  us, one column per lane / R = 1 / R = 4 with 5 workgroups per CU:
+//   b = 8   27.5k rows 31 / 20.5,  55.5k 93 / 80 / 100,  80k - / 136 / 146,  117k 254 / 220 / 208
+//           (float64 values 264 / 235 / 223)
+//   b = 16  27.5k rows 32.8 / 25.8 (k_spmm_wide / R = 1),  55.5k 109 / 105,  117k 312 / 322 (R = 4: 312)
+// Widths up to 4 gain nothing (n = 117k, b = 4: 178 / 176 / 190).
+template <int L, int R, typename VT>
+__global__ __launch_bounds__(256) void k_spmm_rows(int64_t n, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ col, const VT* __restrict__ val,
+                                                   const double* __restrict__ X, uint32_t ldx,
+                                                   double* __restrict__ Y, int64_t ldy) {
+  constexpr int G = 64 / L;
+  const int lane = threadIdx.x & 63, g = lane / L, c = (lane % L) * 2;
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
+  if (r0 >= n) return;
+  // lane i <= R: first nonzero of row r0 + i relative to the first row's (R n < 2^31)
+  const int64_t pb = rp[min<int64_t>(n, r0 + min(lane, R))];
+  const int64_t base = rp[r0];
+  const int off = (int)(pb - base);
+  int longest = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    longest = max(longest, __builtin_amdgcn_readlane(off, i + 1) - __builtin_amdgcn_readlane(off, i));
+  col += base;
+  val += base;
+  f64x2 acc[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) acc[i] = f64x2{0.0, 0.0};
+  auto fetch = [&](int i, int w, int32_t& fc, VT& fv, int& fn) {
+    const int b = __builtin_amdgcn_readlane(off, i) + w, e = __builtin_amdgcn_readlane(off, i + 1);
+    fn = min(64, e - b);
+    fc = 0;
+    fv = VT(0);
+    if (lane < fn) {
+      fc = __builtin_nontemporal_load(col + b + lane);
+      fv = __builtin_nontemporal_load(val + b + lane);
+    }
+  };
+  int32_t mc, mc2;
+  VT mv, mv2;
+  int cnt, cnt2;
+  fetch(0, 0, mc, mv, cnt);
+  for (int w = 0; w < longest; w += 64) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      fetch(i + 1 < R ? i + 1 : 0, i + 1 < R ? w : w + 64, mc2, mv2, cnt2);
+      if (cnt == 64) {
+#pragma unroll
+        for (int s0 = 0; s0 < 64; s0 += G) {
+          const int32_t cc = __shfl(mc, s0 + g);
+          const double vv = (double)__shfl(mv, s0 + g);
+          const f64x2 xv = *(const f64x2*)(X + (uint64_t)(uint32_t)cc * ldx + c);
+          acc[i].x = fma(vv, xv.x, acc[i].x);
+          acc[i].y = fma(vv, xv.y, acc[i].y);
+        }
+      } else {
+        for (int s0 = 0; s0 < cnt; s0 += G) {
+          const int32_t cc = __shfl(mc, s0 + g);
+          const double vv = (double)__shfl(mv, s0 + g);
+          if (s0 + g < cnt) {
+            const f64x2 xv = *(const f64x2*)(X + (uint64_t)(uint32_t)cc * ldx + c);
+            acc[i].x = fma(vv, xv.x, acc[i].x);
+            acc[i].y = fma(vv, xv.y, acc[i].y);
+          }
+        }
+      }
+      mc = mc2;
+      mv = mv2;
+      cnt = cnt2;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+#pragma unroll
+    for (int o = L; o < 64; o <<= 1) {
+      acc[i].x += __shfl_xor(acc[i].x, o);
+      acc[i].y += __shfl_xor(acc[i].y, o);
+    }
+    if (g == 0 && r0 + i < n) {
+      Y[(r0 + i) * ldy + c] = acc[i].x;
+      Y[(r0 + i) * ldy + c + 1] = acc[i].y;
+    }
+  }
+}
+
 template <typename VT, typename XT>
 void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, double* Y, int64_t ldy,
                  int b, const double* shift, hipStream_t s, double ea = 0.0, double ec = 0.0,
@@ -472,6 +561,19 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   if (H.n == 0) return;
   const int64_t grid = cdiv(H.n, 4);
   if constexpr (sizeof(XT) == 8) {
+    // plain products of a whole matrix: width 8, and width 16 while X (n <= 65536: 8 MiB) is not far beyond L2
+    if ((b == 8 || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 &&
+        ldx < (1 << 30) && ((uintptr_t)X & 15) == 0) {
+      // four rows per wave from 100000 rows (X of 6.4 MB); 32 KB of LDS per workgroup leave room for 5 on a CU
+      if (b == 8 && H.n >= 100000 && H.n < (1 << 29))
+        k_spmm_rows<4, 4, VT><<<cdiv(H.n, 16), 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      else if (b == 8)
+        k_spmm_rows<4, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      else
+        k_spmm_rows<8, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      SPPC_LAUNCH_CHECK();
+      return;
+    }
     if (b > 8 && b % 2 == 0 && !dg && ldx % 2 == 0 && ((uintptr_t)X & 15) == 0) {
       if (b <= 16)
         k_spmm_wide<16, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec,
