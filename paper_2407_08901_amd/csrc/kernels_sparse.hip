@@ -377,18 +377,31 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restri
       mc = __builtin_nontemporal_load(&col[base + lane]);
       mv = __builtin_nontemporal_load(&val[base + lane]);
     }
+    auto add = [&](VT vv, XT xv) {
+      if constexpr (sizeof(XT) == 4) return acc + (double)(vv * xv);  // float32 product, float64 accumulation
+      else return fma((double)vv, (double)xv, acc);
+    };
+    // A full window has no bounds checks and its gathers are issued together; lanes beyond b repeat column 0.
+    // us, before / after, n = 117k: float32 X b = 4 164 / 155, 8 227 / 166, 16 411 / 225, 32 734 / 339; float64
+    // X b = 6 260 / 240, 27 879 / 835; n = 27.5k, float32 X 21.0 / 19.5, 28.5 / 23.0, 42 / 30, 77 / 49.  The
+    // narrower widths are bound by the line rate of the gathers and lose up to 6% (float64 X b = 2 163 / 172,
+    // b = 3 187 / 195).
+    if (B >= (sizeof(XT) == 4 ? 4 : 8) && cnt == 64) {
+      const XT* xc = X + (colok ? c : 0);
+#pragma unroll
+      for (int s0 = 0; s0 < 64; s0 += G) {
+        const int32_t cc = __shfl(mc, s0 + g);
+        const VT vv = __shfl(mv, s0 + g);
+        const double sum = add(vv, xc[(int64_t)cc * ldx]);
+        acc = dg && cc == row ? acc : sum;
+      }
+    } else {
 #pragma unroll 4
-    for (int s0 = 0; s0 < cnt; s0 += G) {
-      const int e = s0 + g;
-      const int32_t cc = __shfl(mc, e);
-      const VT vv = __shfl(mv, e);
-      if (e < cnt && colok && !(dg && cc == row)) {
-        const XT xv = X[(int64_t)cc * ldx + c];
-        if constexpr (sizeof(XT) == 4) {
-          acc += (double)(vv * xv);            // float32 product, float64 accumulation
-        } else {
-          acc = fma((double)vv, (double)xv, acc);
-        }
+      for (int s0 = 0; s0 < cnt; s0 += G) {
+        const int e = s0 + g;
+        const int32_t cc = __shfl(mc, e);
+        const VT vv = __shfl(mv, e);
+        if (e < cnt && colok && !(dg && cc == row)) acc = add(vv, X[(int64_t)cc * ldx + c]);
       }
     }
   }
