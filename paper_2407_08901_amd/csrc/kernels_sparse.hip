@@ -574,12 +574,14 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   if (H.n == 0) return;
   const int64_t grid = cdiv(H.n, 4);
   if constexpr (sizeof(XT) == 8) {
-    // plain products of a whole matrix: width 8, and width 16 while X (n <= 65536: 8 MiB) is not far beyond L2
-    if ((b == 8 || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 &&
+    // plain products of a whole matrix: widths 4 and 8, and width 16 while X (n <= 65536: 8 MiB) is not far beyond L2
+    if ((b == 4 || b == 8 || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 &&
         ldx < (1 << 30) && ((uintptr_t)X & 15) == 0) {
       // four rows per wave from 100000 rows (X of 6.4 MB); 32 KB of LDS per workgroup leave room for 5 on a CU
       if (b == 8 && H.n >= 100000 && H.n < (1 << 29))
         k_spmm_rows<4, 4, VT><<<cdiv(H.n, 16), 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      else if (b == 4)
+        k_spmm_rows<2, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else if (b == 8)
         k_spmm_rows<4, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else
