@@ -907,6 +907,17 @@ __global__ void k_pad_copy(int64_t n, int b, const XT* __restrict__ X, int64_t l
   if (c < b) Xp[i] = X[r * ldx + c];
 }
 
+inline int panel_cus() {
+  static int cus = 0;
+  if (cus == 0) {
+    int dev = 0, c = 0;
+    SPPC_HIP(hipGetDevice(&dev));
+    SPPC_HIP(hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev));
+    cus = std::max(1, c);
+  }
+  return cus;
+}
+
 // Workgroups of one launch start together and sweep the panels in step.  The blocks run in
 // rounds of exactly BPC workgroups per compute unit, one launch each: every CU then carries the
 // same load, so the workgroups progress at the same rate and stay within a few panels of each
@@ -915,20 +926,175 @@ __global__ void k_pad_copy(int64_t n, int b, const XT* __restrict__ X, int64_t l
 template <int B, int NW, int D, bool RUNS, typename VT, typename XT>
 void spmm_panel_rounds(const PanelH& P, const VT* val, const XT* Xc, double* Y, int64_t ldy, int b, int bpc,
                        hipStream_t s, const double* X64, int64_t ldx64) {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    SPPC_HIP(hipGetDevice(&dev));
-    SPPC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cus = std::max(1, cus);
-  }
-  const int per = cus * bpc;
+  const int per = panel_cus() * bpc;
   for (int r0 = 0; r0 < P.nblocks; r0 += per) {
     const int nb = std::min(per, P.nblocks - r0);
     k_spmm_panel<B, NW, D, RUNS, VT, XT><<<nb, NW * 64, 0, s>>>(P.n, P.bstart, P.bcount, P.ent, val, Xc, Y, ldy, b, r0, P.dg,
                                                        X64, ldx64);
   }
   SPPC_LAUNCH_CHECK();
+}
+
+// ---- one column: the panel of X in LDS
+//
+// A gathered element of a single column still costs the line rate of a row (0.96 ns per CU from L2).  Here
+// a workgroup brings each panel of X to LDS (global loads straight to LDS, 1 KB per wave), and its waves take a
+// row block each: a wave goes through the stream of its block, 4 consecutive entries per lane and up to two
+// batches of 1024 entries ahead, and joins the workgroup's next panel when an entry lies beyond this one, so
+// every wave passes every panel once.  X is read once per workgroup instead of once per entry.  Entries of one
+// row are summed in the lane before their LDS add: with one entry per lane the adds of neighbouring lanes to
+// one row took 60% of the time.  What bounds it now: the latency of a batch per panel, then HBM (n = 772k
+// 4.7 TB/s).  us, gathers from L2 / this:
+//   d = 200  n = 1.17M  float64 X 1050 / 612, float32 X 920 / 462, float64 values 1060 / 795;  172k 187 / 175
+//   d = 300  n = 386k 524 / 314, 772k 1018 / 389;  d = 60  n = 305k 107 / 91
+constexpr int SPMV_T = 4;             // tiles of 256 entries per batch
+constexpr int SPMV_NW = 16;           // most waves of a workgroup
+constexpr int SPMV_LDS = 160 * 1024;  // of a CU
+
+template <typename VT, typename XT>
+__global__ __launch_bounds__(64 * SPMV_NW) void k_spmv_panel(int64_t n, int nblocks, int PW, int P,
+                                                     const int64_t* __restrict__ bstart,
+                                                     const int32_t* __restrict__ bcount,
+                                                     const uint32_t* __restrict__ ent,
+                                                     const VT* __restrict__ pval, const XT* __restrict__ X,
+                                                     double* __restrict__ Y, int64_t ldy,
+                                                     const double* __restrict__ dg,
+                                                     const double* __restrict__ X64, int64_t ldx64) {
+  extern __shared__ char smem[];
+  const int t = threadIdx.x, nt = blockDim.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  XT* xs = (XT*)smem;                                       // PW elements (a multiple of 4)
+  double* ysh = (double*)(smem + (size_t)PW * sizeof(XT));  // 256 rows per wave
+  const int blk = blockIdx.x * (nt >> 6) + w;
+  double* yw = ysh + w * PANEL_RB;
+  for (int i = lane; i < PANEL_RB; i += 64) yw[i] = 0.0;
+  constexpr int W = 16 / (int)sizeof(XT);
+  // panel p of X into LDS, between barriers: every wave comes here once per panel
+  auto stage = [&](int p) {
+    __syncthreads();
+    const XT* xp = X + (int64_t)p * PW;
+    const int64_t m = min<int64_t>(PW, n - (int64_t)p * PW);
+    if (m == PW && PW % (64 * W) == 0) {  // straight to LDS, 1 KB per wave and load, all in flight together
+      for (int e = w * 64 * W; e < PW; e += nt * W)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xp + e + lane * W),
+                                         (__attribute__((address_space(3))) void*)(xs + e), 16, 0, 0);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+      for (int i = t; i < m; i += nt) xs[i] = xp[i];
+    }
+    __syncthreads();
+  };
+  const bool have = blk < nblocks;
+  const int64_t s0 = have ? bstart[blk] : 0;
+  const uint32_t cnt = have ? (uint32_t)bcount[blk] : 0u;  // below 2^31
+  ent += s0;
+  pval += s0;
+  // lane l of a tile of 256 takes entries 4 l .. 4 l + 3 (the stream is padded to a multiple of 8)
+  uint32_t cw[SPMV_T][4], nw[SPMV_T][4];
+  VT cv[SPMV_T][4], nv[SPMV_T][4];
+  auto load = [&](uint32_t e0) {
+#pragma unroll
+    for (int q = 0; q < SPMV_T; ++q) {
+      const uint32_t e = e0 + q * 256 + 4 * lane;
+      if (e < cnt) {
+        stream_load<uint32_t, 4>(ent + e, nw[q]);
+        stream_load<VT, 4>(pval + e, nv[q]);
+      }
+    }
+  };
+  load(0);
+  int p = 0;
+  stage(0);
+  for (uint32_t e0 = 0; e0 < cnt; e0 += SPMV_T * 256) {
+#pragma unroll
+    for (int q = 0; q < SPMV_T; ++q)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        cw[q][u] = nw[q][u];
+        cv[q][u] = nv[q][u];
+      }
+    load(e0 + SPMV_T * 256);
+#pragma unroll
+    for (int q = 0; q < SPMV_T; ++q) {
+      const uint32_t e = e0 + q * 256 + 4 * lane;
+      const int left = e < cnt ? (int)min(4u, cnt - e) : 0;  // entries done .. left - 1 remain
+      int done = 0;
+      while (true) {
+        // the entries of this panel are the next ones; sums over runs of a row, one LDS add each
+        XT xv[4];
+        int lc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          lc[u] = (int)(cw[q][u] & 0xFFFFFFu) - p * PW;
+          xv[u] = xs[u >= done && u < left && lc[u] < PW ? lc[u] : 0];
+        }
+        double run = 0.0;
+        uint32_t cur = 0;
+        bool open = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (u >= done && u < left && lc[u] < PW) {
+            const uint32_t r = cw[q][u] >> 24;
+            if (open && r != cur) {
+              atomicAdd(yw + cur, run);
+              run = 0.0;
+            }
+            cur = r;
+            open = true;
+            if constexpr (sizeof(XT) == 4) run += (double)((float)cv[q][u] * xv[u]);
+            else run = fma((double)cv[q][u], xv[u], run);
+            done = u + 1;
+          }
+        }
+        if (open) atomicAdd(yw + cur, run);
+        if (__ballot(done < left) == 0) break;
+        stage(++p);
+      }
+    }
+  }
+  while (p + 1 < P) stage(++p);
+  __syncthreads();
+  if (have) {
+    const int64_t row0 = (int64_t)blk * PANEL_RB;
+    for (int i = lane; i < PANEL_RB; i += 64) {
+      const int64_t row = row0 + i;
+      if (row >= n) break;
+      double y = yw[i];
+      if (X64) y = fma(dg[row], X64[row * ldx64], y);
+      else if constexpr (sizeof(XT) == 4) y += (double)((float)dg[row] * X[row]);
+      else y = fma(dg[row], X[row], y);
+      Y[row * ldy] = y;
+    }
+  }
+}
+
+struct SpmvShape {
+  int waves = 0;  // row blocks per workgroup; 0: the kernel does not apply
+  int width = 0;  // columns staged at a time
+};
+
+// As many whole panels at a time as leave LDS for the row sums, and the workgroup size with the least cost in
+// clocks (the largest within 5%: its rounds end with fewer workgroups side by side): per round over the CUs
+// and panel 1300 and the panel's bytes at 60 per clock, per tile of 256 entries 920 and 80 for each wave (within
+// 30% of the measurements above).  Where that exceeds the gathers from L2 (0.0108 clocks per nonzero of the
+// matrix, 4.5 ps), as for few entries per row and panel, and for X beyond the MALL, they stay.
+inline SpmvShape spmv_shape(const PanelH& P, int64_t elem, int cus) {
+  SpmvShape best;
+  if (P.PW % 4) return best;
+  double least = 0.0108 * P.run * (double)P.n * P.P;
+  for (int w = 4; w <= SPMV_NW; ++w) {
+    const int64_t mult = std::min<int64_t>((SPMV_LDS - (int64_t)w * PANEL_RB * 8) / elem / P.PW, P.P);
+    if (mult < 1) continue;
+    const double tiles = P.run * mult * PANEL_RB / 256.0 + 1.0;
+    const double cost = (double)cdiv(cdiv(P.nblocks, w), cus) * (double)cdiv(P.P, mult) *
+                        (1300.0 + (double)(mult * P.PW * elem) / 60.0 + tiles * (920.0 + 80.0 * w));
+    if (cost < (best.waves ? 1.05 : 1.0) * least) {
+      best.waves = w;
+      best.width = (int)(mult * P.PW);
+      least = std::min(least, cost);
+    }
+  }
+  return best;
 }
 
 // X is read from a copy with row stride B when the caller's X is not in that layout: the copy goes
@@ -963,6 +1129,19 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
   // (its rows then come from HBM at longer latency, and more rows in flight per CU pay), and for
   // widths up to 8, whose accumulators leave LDS for as many rows in flight.
   const bool big = (int64_t)P.n * 16 * (int64_t)sizeof(XT) > ((int64_t)256 << 20);
+  if constexpr (B == 1) {
+    const SpmvShape h = big ? SpmvShape() : spmv_shape(P, sizeof(XT), panel_cus());
+    if (h.waves > 0) {
+      const size_t lds = (size_t)h.width * sizeof(XT) + (size_t)h.waves * PANEL_RB * 8;
+      SPPC_HIP(hipFuncSetAttribute((const void*)k_spmv_panel<VT, XT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   SPMV_LDS));
+      k_spmv_panel<VT, XT><<<cdiv(P.nblocks, h.waves), h.waves * 64, lds, s>>>(
+          P.n, P.nblocks, h.width, (int)cdiv(P.n, h.width), P.bstart, P.bcount, P.ent, val, Xc, Y, ldy, P.dg, X64,
+          ldx64);
+      SPPC_LAUNCH_CHECK();
+      return;
+    }
+  }
   // Sums over runs of a row's entries where a row has several in a panel (run = their mean): the LDS adds
   // of the wider products are their bound, and a run costs one set.  Measured (ms, without / with):
   //   float32 X  b = 8:   run 1.4 1.54 / 1.42, 2.8 1.55 / 1.44 (n = 1.17M), 3.2 1.51 / 1.32 (772k),
