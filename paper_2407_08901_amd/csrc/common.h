@@ -169,6 +169,9 @@ void gemm_tn(int64_t n, int m, int b, const double* A, int64_t lda, const double
 // Y[n x b] (ldy) = beta*Y + alpha * A[n x m] C[m x b]   (C row-major, ldc)
 void gemm_nn(int64_t n, int m, int b, const double* A, int64_t lda, const double* C, int64_t ldc,
              double* Y, int64_t ldy, double alpha, double beta, hipStream_t s);
+// Y = beta*Y0 + alpha * A C with Y0 (ldy0) apart from Y
+void gemm_nn_from(int64_t n, int m, int b, const double* A, int64_t lda, const double* C, int64_t ldc,
+                  const double* Y0, int64_t ldy0, double* Y, int64_t ldy, double alpha, double beta, hipStream_t s);
 // One pass over A for two products: Y1[n x b1] (ldy1) = beta1*Y1 + A C[:, 0:b1] and
 // Y2[n x b2] (ldy2) = beta2*Y2 + A C[:, b1:b1+b2], with b1 + b2 <= 32 (C row-major, ldc).
 void gemm_nn2(int64_t n, int m, int b1, int b2, const double* A, int64_t lda, const double* C, int64_t ldc,
