@@ -113,6 +113,20 @@ __global__ __launch_bounds__(256) void k_gemm_tn(int64_t n, int m, int b, const 
   }
 }
 
+// part[c stride], c = lane, lane + 64, ..., added in this order by a lane; 4 loads at a time (one at a time a
+// sum of 1024 chunks waited for 16 loads in turn: 7.8 -> 5.9 us, 154 chunks 3.1 -> 2.7 us)
+__device__ inline double lane_partials(const double* __restrict__ part, int64_t nchunks, int64_t stride, int lane) {
+  double s = 0.0;
+  for (int64_t c = lane; c < nchunks; c += 256) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = c + 64 * u < nchunks ? part[(c + 64 * u) * stride] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += v[u];
+  }
+  return s;
+}
+
 // one wave per output element: lanes stride over the chunks, fixed-order tree sum
 __global__ void k_reduce_partials(int64_t nchunks, int m, int b, const double* __restrict__ part,
                                   double* __restrict__ C, int64_t ldc, double alpha, double beta) {
@@ -120,8 +134,7 @@ __global__ void k_reduce_partials(int64_t nchunks, int m, int b, const double* _
   const int lane = threadIdx.x & 63;
   if (e >= (int64_t)m * b) return;
   const int64_t mb = (int64_t)m * b;
-  double s = 0.0;
-  for (int64_t c = lane; c < nchunks; c += 64) s += part[c * mb + e];
+  double s = lane_partials(part + e, nchunks, mb, lane);
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if (lane == 0) {
     const int i = (int)(e / b), j = (int)(e % b);
@@ -281,8 +294,7 @@ __global__ void k_colreduce_final(int64_t nchunks, int b, const double* __restri
   const int j = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (j >= b) return;
-  double s = 0.0;
-  for (int64_t c = lane; c < nchunks; c += 64) s += part[c * b + j];
+  double s = lane_partials(part + j, nchunks, b, lane);
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if (lane == 0) out[j] = s;
 }
