@@ -129,8 +129,8 @@ __global__ void k_full_rowptr(int64_t n, const int64_t* __restrict__ lower_rp,
 // digit's peers in a round come from ballots over the digit's bits, and a wave's runs follow
 // those of the waves before it), so every entry keeps its order among equal digits.  No global
 // atomics, and the result does not depend on scheduling.
-constexpr int RS_WAVES = 4;                 // waves per tile
-constexpr int RS_WTILE = 2048;              // entries per wave
+constexpr int RS_WAVES = 16;                // waves per tile
+constexpr int RS_WTILE = 512;               // entries per wave
 constexpr int RS_TILE = RS_WAVES * RS_WTILE;
 constexpr int RS_ROUNDS = RS_WTILE / 64;
 
@@ -174,7 +174,10 @@ __global__ __launch_bounds__(256) void k_rs_hist(int64_t m, const int32_t* __res
 // with digit d), ranks taken in tile order.  The tile is first reordered by digit in LDS
 // (stable), then written out in that order, so consecutive lanes write consecutive positions of
 // one digit's run and the stores coalesce: a tile of 8192 entries holds runs of 32 entries on
-// average for 256 digits (a one-wave tile of 2048 left runs of 8, 32-byte stores of each array).
+// average for 256 digits (a one-wave tile of 2048 left runs of 8, 32-byte stores of each array).  The tile fills
+// the LDS of a CU, so its waves are all that hide the chain of a round: with 4 waves of 2048 entries a pass of
+// n = 1.17M, d = 200 took 1.24 ms, with 8 of 1024 0.94, with 16 of 512 0.84 (n = 386k 0.58, 0.41, 0.37; n = 7.72M
+// 13.3, 14.0, 13.2); tiles of 4096 entries 0.9-1.1.
 template <typename TT>
 __global__ __launch_bounds__(64 * RS_WAVES) void k_rs_scatter(int64_t m, const int32_t* __restrict__ kin,
                                                               const int32_t* __restrict__ rin,
