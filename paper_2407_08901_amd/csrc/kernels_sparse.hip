@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restri
                                               const double* __restrict__ shift, double ea, double ec,
                                               double eb, const double* __restrict__ Zo, int64_t ldz,
                                               const double* __restrict__ dg, const double* __restrict__ X64,
-                                              int64_t ldx64) {
+                                              int64_t ldx64, int full) {
   constexpr int G = 64 / B;
   const int lane = threadIdx.x & 63;
   const int g = lane / B;
@@ -388,8 +388,9 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restri
     // us, before / after, n = 117k: float32 X b = 4 164 / 155, 8 227 / 166, 16 411 / 225, 32 734 / 339; float64
     // X b = 6 260 / 240, 27 879 / 835; n = 27.5k, float32 X 21.0 / 19.5, 28.5 / 23.0, 42 / 30, 77 / 49.  The
     // narrower widths are bound by the line rate of the gathers and lose up to 6% (float64 X b = 2 163 / 172,
-    // b = 3 187 / 195).
-    if (B >= (sizeof(XT) == 4 ? 4 : 8) && cnt == 64) {
+    // b = 3 187 / 195); so do float64 X of width 5 to 8 from 200000 rows, where X is far beyond L2 and more gathers
+    // per wave spread the waves over its columns (n = 281k, b = 6 818 / 862): full = 0 there.
+    if (B >= (sizeof(XT) == 4 ? 4 : 8) && full && cnt == 64) {
       const XT* xc = X + (colok ? c : 0);
 #pragma unroll
       for (int s0 = 0; s0 < 64; s0 += G) {
@@ -488,7 +489,9 @@ __global__ __launch_bounds__(256) void k_spmm_wide(int64_t n, const int64_t* __r
 //   b = 8   27.5k rows 31 / 20.5,  55.5k 93 / 80 / 100,  80k - / 136 / 146,  117k 254 / 220 / 208
 //           (float64 values 264 / 235 / 223)
 //   b = 16  27.5k rows 32.8 / 25.8 (k_spmm_wide / R = 1),  55.5k 109 / 105,  117k 312 / 322 (R = 4: 312)
-// Widths up to 4 gain nothing (n = 117k, b = 4: 178 / 176 / 190).
+//   b = 4   4900 rows 5.0 / 4.6 (a call),  27.5k 22.5 / 18.4,  117k 168 / 158 / 172
+// and with degree 196:  b = 8  216k 547 / 545 / 524,  281k 775 / 777 / 756 to 788
+//   b = 4   216k 360 / 357 / 354,  281k 552 / 575 / 531,  416k 1060 / 1047 / 987 to 1012
 template <int L, int R, typename VT>
 __global__ __launch_bounds__(256) void k_spmm_rows(int64_t n, const int64_t* __restrict__ rp,
                                                    const int32_t* __restrict__ col, const VT* __restrict__ val,
@@ -577,14 +580,19 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   if (H.n == 0) return;
   const int64_t grid = cdiv(H.n, 4);
   if constexpr (sizeof(XT) == 8) {
-    // plain products of a whole matrix: widths 4 and 8, and width 16 while X (n <= 65536: 8 MiB) is not far beyond L2
-    if ((b == 4 || b == 8 || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 &&
-        ldx < (1 << 30) && ((uintptr_t)X & 15) == 0) {
-      // four rows per wave from 100000 rows (X of 6.4 MB); 32 KB of LDS per workgroup leave room for 5 on a CU
-      if (b == 8 && H.n >= 100000 && H.n < (1 << 29))
-        k_spmm_rows<4, 4, VT><<<cdiv(H.n, 16), 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+    // Plain products of a whole matrix: width 4; widths 8 and 16 while X (n < 250000, n <= 65536: 16 and 8 MB) is not
+    // far beyond L2 (b = 8: 216k rows 547 / 524 us, from 281k on even within the 3% that two processes differ by).
+    if ((b == 4 || (b == 8 && H.n < 250000) || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend &&
+        ldx % 2 == 0 && ldx < (1 << 30) && ((uintptr_t)X & 15) == 0) {
+      // Four rows per wave where X is beyond L2 (from 100000 rows of 64 bytes, 200000 of 32), and 32 KB of LDS per
+      // workgroup, which leave room for 5 on a CU (b = 4, one row / four: 216k rows 357 / 354, 281k 571 / 531).
+      const int64_t g4 = cdiv(H.n, 16);
+      if (b == 4 && H.n >= 200000 && H.n < (1 << 29))
+        k_spmm_rows<2, 4, VT><<<g4, 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else if (b == 4)
         k_spmm_rows<2, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      else if (b == 8 && H.n >= 100000)
+        k_spmm_rows<4, 4, VT><<<g4, 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else if (b == 8)
         k_spmm_rows<4, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else
@@ -603,9 +611,10 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
       return;
     }
   }
+  const int full = sizeof(XT) == 4 || b > 8 || H.n < 200000;
 #define SPPC_SPMM_CASE(BB)                                                                        \
   k_spmm<BB, VT, XT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec, \
-                                          eb, Zo, ldz, dg, X64, ldx64);                                     \
+                                          eb, Zo, ldz, dg, X64, ldx64, full);                               \
   break;
   switch (b <= 1 ? 1 : b <= 2 ? 2 : b <= 4 ? 4 : b <= 8 ? 8 : b <= 16 ? 16 : 32) {
     case 1: SPPC_SPMM_CASE(1)

@@ -16,7 +16,7 @@ def P():
     return P
 
 
-@pytest.mark.parametrize("n", [65, 1021, 65536, 65537, 99999, 100001])
+@pytest.mark.parametrize("n", [65, 1021, 65536, 65537, 99999, 100001, 200001, 500001])
 def test_row_product(P, n):
     rng = np.random.default_rng(n)
     # rows of 64, 65 and 200 entries and their columns; the others hold the diagonal and a few more
@@ -35,7 +35,7 @@ def test_row_product(P, n):
         H = (V + sp.triu(V, 1).T).tocsr()
         ctx = P.sppc_setup(rp, col, torch.from_numpy(vals).cuda(), np.array([0, 20, n]), 1, 2,
                            P.sppc_default_opts(panel_width=0))
-        for b in (4, 8, 16):
+        for b in (4, 6, 8, 16):
             for off in (0, 1):  # off = 1: X 8 bytes past a 16-byte boundary, the general kernel
                 print("case n=%d f32=%d b=%d off=%d" % (n, f32, b, off), flush=True)
                 buf = torch.from_numpy(rng.standard_normal(n * b + off)).cuda()
