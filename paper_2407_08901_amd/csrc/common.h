@@ -298,7 +298,6 @@ void scatter_cols(int64_t n, int S, const int* idx, const double* X, int64_t ldx
 int mpnn_nparam();
 void mpnn_prepare(const DevCSR& H, const double* diag, const int64_t* level_off_dev, int L, int nsmall, double* lev,
                   double* Ad, double* A1, double* Al, double* tmp, hipStream_t s);
-int64_t mpnn_work_doubles(int64_t n, int S);
 // Optional basis for the output projection t - Q (Q^T t) (training against the part of the
 // exact eigenvector outside the basis); work holds mpnn_basis_work_doubles(n, m) doubles.
 struct MpnnBasis {

@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "common.h"
+#include "partials.h"
 #include "sppc.h"
 
 namespace sppc {

@@ -5,6 +5,7 @@
 // the sparse product in place.  Reductions over rows write one partial per row chunk
 // and are summed in a fixed order (deterministic results).
 #include "common.h"
+#include "partials.h"
 
 namespace sppc {
 
@@ -242,14 +243,6 @@ __global__ __launch_bounds__(256) void k_gemm_nn(int64_t n, int m, int b, const 
 }
 
 // ---------------------------------------------------------------- column reductions
-// Rows per partial sum of the column reductions: about 1024 blocks.  A block has 4 waves and few loads in
-// flight each, so 256 blocks leave most of the bandwidth unused: residual of n = 1.17M, 8 columns 62 us with
-// 286 blocks (3.6 TB/s), 34 us with 916; sum of squares 40 and 18.6 us.
-inline int64_t cr_chunk(int64_t n) {
-  int64_t c = (n / 1024 + 255) / 256 * 256;
-  return c < 256 ? 256 : (c > 4096 ? 4096 : c);
-}
-
 // mode 0: sum X^2 ; mode 1: R = HZ - Z theta and sum R^2 ; mode 2: sum Z[:,idx[a]] * T[:,a]
 template <int MODE>
 __global__ __launch_bounds__(256) void k_colreduce(int64_t n, int b, const double* __restrict__ X,
@@ -470,14 +463,14 @@ void fill_zero(int64_t count, double* p, hipStream_t s) {
 void residual_block(int64_t n, int b, const double* Z, int64_t ldz, const double* HZ, int64_t ldhz,
                     const double* theta, double* R, int64_t ldr, double* sumsq, double* work,
                     hipStream_t s) {
-  const int64_t ch = cr_chunk(n), nch = cdiv(n > 0 ? n : 1, ch);
+  const int64_t ch = cr_chunk(n), nch = cr_chunks(n);
   k_colreduce<1><<<nch, 256, 0, s>>>(n, b, Z, ldz, HZ, ldhz, theta, nullptr, R, ldr, work, ch);
   k_colreduce_final<<<cdiv(b, 4), 256, 0, s>>>(nch, b, work, sumsq);
   SPPC_LAUNCH_CHECK();
 }
 
 void colsumsq(int64_t n, int b, const double* X, int64_t ldx, double* out, double* work, hipStream_t s) {
-  const int64_t ch = cr_chunk(n), nch = cdiv(n > 0 ? n : 1, ch);
+  const int64_t ch = cr_chunk(n), nch = cr_chunks(n);
   k_colreduce<0><<<nch, 256, 0, s>>>(n, b, X, ldx, nullptr, 0, nullptr, nullptr, nullptr, 0, work, ch);
   k_colreduce_final<<<cdiv(b, 4), 256, 0, s>>>(nch, b, work, out);
   SPPC_LAUNCH_CHECK();
@@ -485,7 +478,7 @@ void colsumsq(int64_t n, int b, const double* X, int64_t ldx, double* out, doubl
 
 void paired_dots(int64_t n, int na, const int* idx, const double* Z, int64_t ldz, const double* T,
                  int64_t ldt, double* dots, double* work, hipStream_t s) {
-  const int64_t ch = cr_chunk(n), nch = cdiv(n > 0 ? n : 1, ch);
+  const int64_t ch = cr_chunk(n), nch = cr_chunks(n);
   k_colreduce<2><<<nch, 256, 0, s>>>(n, na, Z, ldz, T, ldt, nullptr, idx, nullptr, 0, work, ch);
   k_colreduce_final<<<cdiv(na, 4), 256, 0, s>>>(nch, na, work, dots);
   SPPC_LAUNCH_CHECK();
@@ -546,7 +539,7 @@ __global__ __launch_bounds__(256) void k_coldots(int64_t n, int b, const double*
 
 void coldots(int64_t n, int b, const double* X, int64_t ldx, const double* Y, int64_t ldy, double* out,
              double* work, hipStream_t s) {
-  const int64_t ch = cr_chunk(n), nch = cdiv(n > 0 ? n : 1, ch);
+  const int64_t ch = cr_chunk(n), nch = cr_chunks(n);
   k_coldots<<<nch, 256, 0, s>>>(n, b, X, ldx, Y, ldy, work, ch);
   k_colreduce_final<<<cdiv(b, 4), 256, 0, s>>>(nch, b, work, out);
   SPPC_LAUNCH_CHECK();

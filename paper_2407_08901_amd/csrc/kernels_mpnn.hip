@@ -12,13 +12,14 @@
 // row sums over samples are deterministic per-block partials added in a fixed order.
 // Parameters: Ws[32x3] | Wn[32x3] | b1[32] | ws[32] | wn[32] | b2  (289).
 #include "common.h"
+#include "partials.h"
 
 namespace sppc {
 
 namespace {
 
 constexpr int HID = 32;
-constexpr int NPAR = 289;
+constexpr int NPAR = MPNN_NPAR;
 
 __device__ inline double clamp_den(double den, double theta) {
   const double fl = 1e-2 * fmax(1.0, fabs(theta));
@@ -122,10 +123,6 @@ __global__ void k_project_x(int64_t n, int S, const double* __restrict__ xdt, co
 
 // Partials over a chunk of rows of t.e, t.t and e.e per sample, one pass over both (three passes of two
 // operands each cost 110 us at n = 386k, S = 16; this one 17 us).  Column q S + s of part: dot q of sample s.
-inline int64_t ld_chunk(int64_t n) {
-  const int64_t c = (n / 1024 + 63) / 64 * 64;
-  return c < 64 ? 64 : c;
-}
 __global__ __launch_bounds__(256) void k_loss_dots(int64_t n, int S, const double* __restrict__ t,
                                                    const double* __restrict__ E, double* __restrict__ part,
                                                    int64_t chunk) {
@@ -195,12 +192,6 @@ __global__ __launch_bounds__(1024) void k_loss_coef(int64_t nch, int S, const do
 // chip idle on small inputs.  n = 4900, S = 4: 51 -> 6.6 us; n = 386k, S = 16: 970 -> 336 us, bound by the
 // issue of the ten conversions and float64 sums per item and unit.
 constexpr int GT = 256;  // items per tile
-
-// items per block: enough blocks for 8 per CU, whole quarter tiles
-inline int64_t grad_items(int64_t items) {
-  const int64_t c = (items / 2048 + 63) / 64 * 64;
-  return c < 64 ? 64 : c;
-}
 
 template <typename T>
 __global__ __launch_bounds__(GT) void k_mpnn_grad(int64_t n, int S, Static st, const T* __restrict__ w,
@@ -409,14 +400,6 @@ void mpnn_prepare(const DevCSR& H, const double* diag, const int64_t* level_off_
   SPPC_LAUNCH_CHECK();
 }
 
-// Workspace layout (n x S doubles each): fr | HF | u | hs | Hu | t | tJ | dO | HdO  (9 n S)
-// + small: sumsq, ca, cb, xdt [S], partial sums.
-int64_t mpnn_work_doubles(int64_t n, int S) {
-  const int64_t items = n * S;
-  const int64_t nblk = cdiv(items, grad_items(items));
-  return 9 * items + 16 * 64 + nblk * NPAR + NPAR + 64;
-}
-
 // Forward (and, with E, the loss gradient) for S samples.  R, X: n x S (leading dims ldr, ldx),
 // theta_dev[S].  T_out (n x S, ld S): the projected output t~ (or nullptr).  grad_out (device,
 // 289 doubles, mean over samples) and loss_dev (S doubles) when E != nullptr.
@@ -455,7 +438,7 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
   double* ca = sm + 64;
   double* cb = sm + 128;
   double* xdt = sm + 192;
-  double* part = sm + 16 * 64;
+  double* part = sm + MPNN_SMALL;
   Static st{diag, lev, Ad, A1, Al};
   // t~ is built in the caller's output where that does not overlap an operand that is still to be read
   auto apart = [&](const double* p, int64_t ld, int64_t cols) {
@@ -489,7 +472,7 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
   }
   if (T_out && t != T_out) copy_block(n, S, t, S, T_out, S, s);
   if (E) {
-    const int64_t lch = ld_chunk(n), lnc = cdiv(n, lch);
+    const int64_t lch = ld_chunk(n), lnc = ld_chunks(n);
     k_loss_dots<<<lnc, 256, 0, s>>>(n, S, t, E, part, lch);
     k_loss_coef<<<1, 1024, 0, s>>>(lnc, S, part, ca, cb, loss_dev, 1.0 / S);
     // dL/dt~ = ca e + cb t~ -> dO ; then through the projection and t = tJ (1 + o)
@@ -502,8 +485,7 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
       k_project_x<<<gg(items), 256, 0, s>>>(n, S, xdt, X, ldx, dO, tJ);
     }
     spmm_f64(H, dO, S, HdO, S, S, nullptr, s);
-    const int64_t ipb = grad_items(items);
-    const int64_t nblk = cdiv(items, ipb);
+    const int64_t ipb = grad_items(items), nblk = grad_blocks(items);
     k_mpnn_grad<T><<<nblk, GT, 0, s>>>(n, S, st, w, fr, HF, theta_dev, dO, HdO, part, ipb);
     k_sum_parts<<<cdiv(NPAR, 4), 256, 0, s>>>(nblk, part, grad_out);
   }
