@@ -111,7 +111,8 @@ typedef struct {
                           float64 default), min(2k, 28, n0) with looser ones (the mixed default); with
                           pair_index j at least j + 2 */
   double tau_drop;     /* new column dropped when sin(angle to the basis) <= tau_drop */
-  double inner_tol;    /* relative residual of the small-space solves; 0 = 1e-12 (FP64) / 1e-6 (MIXED) */
+  double inner_tol;    /* relative residual of the small-space solves; 0 = 1e-12 (FP64) / 1e-6 (MIXED).  Below
+                          1e-9, spaces of up to 256 rows are solved to a tenth of it */
   double h0_tol;       /* residual of the H0hat eigenpairs, relative to max(1,|E|); default 1e-12.
                           The pairs beyond the wanted ones (kept only to deflate the small solves)
                           stop at max(h0_tol, 1e-3 inner_tol): 1e-9 in the mixed form */

@@ -97,7 +97,8 @@ struct DevCSR {
   int32_t* col = nullptr;
   double* val64 = nullptr;     // float64 values (nullptr when val32 is exact and enough)
   float* val32 = nullptr;      // float32 values
-  const PanelH* panel = nullptr;  // optional panel copy used by the plain products (b <= 16)
+  const PanelH* panel = nullptr;  // optional panel copy used by the plain products
+  int longest = 0;             // entries of the longest row (compact_view only)
 };
 
 // Setup: build the full CSR from the upper triangle.  Returns nnz of the full matrix.

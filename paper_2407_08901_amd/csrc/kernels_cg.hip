@@ -458,37 +458,41 @@ __global__ __launch_bounds__(NT) void k_cg_iter(CGArgs a, int j, int* hflag) {
 
 // ---- the whole solve of one system by one workgroup, for small spaces
 //
-// A grid-wide iteration costs a launch (6-8 us between dependent kernels) whatever its size.  Where
-// H0hat and the vectors of one system fit a workgroup, block c runs system c from the projection of its
-// right-hand side to that of its solution, with two workgroup barriers per iteration: the gathered
-// vector and A r in LDS, the other vectors in registers (row t + NTH q of thread t), 8 lanes per row of
-// H0hat, whose entries stream from L2 (64 bytes per clock and CU: the bound beyond a few thousand
-// entries).  n0 = 100, 62 iterations: 0.46 -> 0.08 ms per solve.
+// A grid-wide iteration costs a launch (10.5-12 us with its share of the solve's other kernels) whatever its
+// size.  Where H0hat and the vectors of one system fit a workgroup, block c runs system c from the projection of
+// its right-hand side to that of its solution, with two workgroup barriers per iteration: the gathered vector
+// and A r in LDS, the other vectors in registers (row t of thread t), 8 lanes per row of H0hat, whose entries
+// stream from L2.  us per iteration, one workgroup / one kernel per iteration:
+//   30 entries a row  100 rows 4.2 / 17,  256 rows 4.6 / 15,  505 rows 5.8 / 10.9,  1000 rows 8.8 / 10.8,
+//                     2000 rows 15.1 / 10.9
+//   dense             128 rows 5.8,  200 rows 10.2,  256 rows 12.6,  300 rows 17.9 / 11.6
+//   a row of every column  1000 rows 17.7 / 11.7
+// that is about 3.2 us, 2.6 ns a row, and 0.12 ns an entry or 11 ns an entry of the longest row (a chain of loads
+// by its 8 lanes), whichever is more: cg_one_workgroup.
 //
-// A tight tolerance (below 1e-9) is taken a decade further up to 256 rows: the perturbative orders amplify
-// the error of the solves (on a drifting pair 1e-12 became 2e-10 of the Ritz value at order 12, and 6e-12 with
-// the further decade), and the few more iterations cost 1 us each here.  Beyond 256 rows the margin is 9% of
-// the squared norm.  Any margin serves there; which steps a nearly converged solve takes after the orders
-// depends on what the solves leave at 1e-12, and with this one the hybrid on 505 rows (n = 4276, k = 16) still
-// ends with a check that fails and the float64 refinement, the case that its workspace test is there for.
-constexpr int CGS_MAXN = 6144;
-constexpr int64_t CGS_MAXNNZ = 131072;
+// A tight tolerance (below 1e-9) is taken a decade further here: the perturbative orders amplify the error of the
+// solves (on a drifting pair 1e-12 became 2e-10 of the Ritz value at order 12, and 6e-12 with the further decade),
+// and the few more iterations cost 4 us each.  Beyond 256 rows tight solves keep the kernel per iteration and the
+// tolerance as given: which steps a nearly converged solve takes after the orders follows the rounding of what the
+// solves leave, and that kernel's is what the float64 solves of such spaces always had (this one would be faster up
+// to about 1000 rows: 0.38 against 0.66 ms a solve at 505, 0.75 against 0.82 at 1000).
+constexpr int64_t CGS_MAXN = 1024;
+inline bool cg_one_workgroup(const DevCSR& H0, int64_t n0, double tol) {
+  if (n0 > (tol < 1e-9 ? 256 : CGS_MAXN)) return false;
+  return 22 * n0 + std::max<int64_t>(H0.nnz, 90 * (int64_t)H0.longest) <= 60000;
+}
 
-template <int NTH, int Q>
-__device__ inline void cgs_dots(int64_t n0, int D, const double* __restrict__ Ps, const double (&y)[Q], double* part,
+template <int NTH>
+__device__ inline void cgs_dots(int64_t n0, int D, const double* __restrict__ Ps, double y, double* part,
                                 double* tot) {
   constexpr int NW = NTH / 64;
   const int t = threadIdx.x, w = t >> 6;
   for (int d0 = 0; d0 < D; d0 += 4) {
     double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (t < n0) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int64_t i = t + NTH * q;
-      if (i < n0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (d0 + u < D) s[u] = fma(Ps[i * D + d0 + u], y[q], s[u]);
-      }
+      for (int u = 0; u < 4; ++u)
+        if (d0 + u < D) s[u] = Ps[(int64_t)t * D + d0 + u] * y;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -505,11 +509,11 @@ __device__ inline void cgs_dots(int64_t n0, int D, const double* __restrict__ Ps
   __syncthreads();
 }
 
-template <int NTH, int Q, typename VT>
+template <int NTH, typename VT>
 __global__ __launch_bounds__(NTH) void k_cg_small(CGArgs a, double* coef, int maxit, int* iters) {
-  constexpr int N = NTH * Q, NW = NTH / 64;
-  __shared__ double rs[N], ws[N];
-  __shared__ int off[N + 1];
+  constexpr int NW = NTH / 64;
+  __shared__ double rs[NTH], ws[NTH];
+  __shared__ int off[NTH + 1];
   __shared__ double part[NW * CG_MAXD], tot[CG_MAXD];
   __shared__ double red[2][2 * NW];
   const int t = threadIdx.x, w = t >> 6, ln = t & 63;
@@ -517,32 +521,20 @@ __global__ __launch_bounds__(NTH) void k_cg_small(CGArgs a, double* coef, int ma
   const VT* __restrict__ val = sizeof(VT) == 8 ? (const VT*)a.v64 : (const VT*)a.v32;
   const int32_t* __restrict__ col = a.col;
   const double sh = a.shift[c];
-  const double tol2 = a.tol2 < 1e-18 ? (a.n0 <= 256 ? 0.01 : 0.914) * a.tol2 : a.tol2;
+  const double tol2 = a.tol2 < 1e-18 ? 0.01 * a.tol2 : a.tol2;
   for (int i = t; i <= n0; i += NTH) off[i] = (int)a.rp[i];
-  double r[Q], p[Q], s[Q], x[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int i = t + NTH * q;
-    r[q] = i < n0 ? a.r0[(int64_t)i * k + c] : 0.0;
-    p[q] = s[q] = x[q] = 0.0;
-  }
-  cgs_dots<NTH, Q>(n0, D, a.Ps, r, part, tot);
+  double r = t < n0 ? a.r0[(int64_t)t * k + c] : 0.0, p = 0.0, s = 0.0, x = 0.0;
+  cgs_dots<NTH>(n0, D, a.Ps, r, part, tot);
   if (t < D) coef[t * k + c] = tot[t];
-  auto project = [&](double (&y)[Q]) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int i = t + NTH * q;
-      if (i < n0)
-        for (int d = 0; d < D; ++d) y[q] -= a.Ps[(int64_t)i * D + d] * tot[d];
-    }
+  auto project = [&](double& y) {
+    if (t < n0)
+      for (int d = 0; d < D; ++d) y -= a.Ps[(int64_t)t * D + d] * tot[d];
   };
   project(r);
   double gold = 0.0, aold = 0.0, bb = 0.0;
   int j = 0;
   for (;; ++j) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (t + NTH * q < n0) rs[t + NTH * q] = r[q];
+    if (t < n0) rs[t] = r;
     __syncthreads();
     // w = (H0hat - shift) r and the partial sums of (r.r, w.r): 8 lanes per row
     double sg = 0.0, sd = 0.0;
@@ -593,36 +585,26 @@ __global__ __launch_bounds__(NTH) void k_cg_small(CGArgs a, double* coef, int ma
     if (!now || j >= maxit) break;  // the same in every thread
     gold = g;
     aold = al;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int i = t + NTH * q;
-      if (i < n0) {
-        p[q] = fma(be, p[q], r[q]);
-        s[q] = fma(be, s[q], ws[i]);
-        x[q] = fma(al, p[q], x[q]);
-        r[q] = fma(-al, s[q], r[q]);
-      }
+    if (t < n0) {
+      p = fma(be, p, r);
+      s = fma(be, s, ws[t]);
+      x = fma(al, p, x);
+      r = fma(-al, s, r);
     }
   }
   if (t == 0) iters[c] = j;
   // x <- P x (removes the drift into the deflated directions)
-  cgs_dots<NTH, Q>(n0, D, a.Ps, x, part, tot);
+  cgs_dots<NTH>(n0, D, a.Ps, x, part, tot);
   project(x);
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int i = t + NTH * q;
-    if (i < n0) a.x[(int64_t)i * k + c] = x[q];
-  }
+  if (t < n0) a.x[(int64_t)t * k + c] = x;
 }
 
 template <typename VT>
 void launch_small(const CGArgs& a, double* coef, int maxit, int* iters, hipStream_t s) {
-  const int64_t n0 = a.n0;
-  if (n0 <= 256) k_cg_small<256, 1, VT><<<a.k, 256, 0, s>>>(a, coef, maxit, iters);
-  else if (n0 <= 1024) k_cg_small<1024, 1, VT><<<a.k, 1024, 0, s>>>(a, coef, maxit, iters);
-  else if (n0 <= 2048) k_cg_small<1024, 2, VT><<<a.k, 1024, 0, s>>>(a, coef, maxit, iters);
-  else if (n0 <= 4096) k_cg_small<1024, 4, VT><<<a.k, 1024, 0, s>>>(a, coef, maxit, iters);
-  else k_cg_small<1024, 6, VT><<<a.k, 1024, 0, s>>>(a, coef, maxit, iters);
+  // 16 waves from 64 rows on (us an iteration with 4 / 16 waves: 24 rows 1.1 / 1.7, 64 rows 4.3 / 4.4, 100 rows
+  // 4.9 / 4.2, 256 rows 8.9 / 4.6, dense 200 rows 27 / 10)
+  if (a.n0 <= 64) k_cg_small<256, VT><<<a.k, 256, 0, s>>>(a, coef, maxit, iters);
+  else k_cg_small<1024, VT><<<a.k, 1024, 0, s>>>(a, coef, maxit, iters);
   SPPC_LAUNCH_CHECK();
 }
 
@@ -687,7 +669,7 @@ int cg_solve(const DevCSR& H0, int64_t n0, int k, int D, const double* shift, co
   const int64_t vs = n0 * CG_MAXK;
   CGArgs a{n0, k, D, H0.rp, H0.rend, H0.col, H0.val64, H0.val32, shift, Ps, rowb, x,
            r, {vec, vec + 3 * vs}, vec + 6 * vs, vec + 7 * vs, {part0, part1}, partP, nb2, sc, tol * tol};
-  if (n0 <= CGS_MAXN && H0.nnz <= CGS_MAXNNZ) {
+  if (cg_one_workgroup(H0, n0, tol)) {
     int* iters = sc->act[0];
     if (H0.val64) launch_small<double>(a, ccoef, maxit, iters, s);
     else launch_small<float>(a, ccoef, maxit, iters, s);

@@ -31,7 +31,8 @@ constexpr int EIG_MAX = 512;
 constexpr int EIG_BUF = 16384;    // doubles of LDS work space
 constexpr int EIG_HV = EIG_T * (EIG_T - 1) / 2;  // packed Householder vectors of the trailing block
 
-// 1 / b refined by two Newton-Raphson steps; b nonzero, finite, and of ordinary size
+// 1 / b refined by two Newton-Raphson steps (relative error 4.6e-8 of the hardware's, 2.1e-15 after one step,
+// 1.1e-16 after two); b nonzero, finite, and of ordinary size
 __device__ inline double fast_rcp(double b) {
   double r = __builtin_amdgcn_rcp(b);
   r = fma(r, fma(-b, r, 1.0), r);
@@ -127,8 +128,7 @@ __device__ __forceinline__ void inverse_iteration(int m, int nw, const double* d
         const double yn = start();
         const bool sw = fabs(ca) < fabs(ee[u]);
         const double pv = away(sw ? ee[u] : ca);
-        double r = __builtin_amdgcn_rcp(pv);
-        r = fma(r, fma(-pv, r, 1.0), r);
+        const double r = fast_rcp(pv);
         const double mult = (sw ? ca : ee[u]) * r;
         b1[u] = sw ? na[u] : cb;
         by[u] = sw ? yn : cur;

@@ -630,9 +630,12 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
 
 // rows [0, n0) restricted to columns < n0 (the row ends of the view), copied contiguously
 __global__ void k_view_count(int64_t n0, const int64_t* __restrict__ rp, const int64_t* __restrict__ rend,
-                             int32_t* __restrict__ cnt) {
+                             int32_t* __restrict__ cnt, int* __restrict__ longest) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n0) cnt[i] = (int32_t)(rend[i] - rp[i]);
+  int len = 0;
+  if (i < n0) cnt[i] = len = (int32_t)(rend[i] - rp[i]);
+  for (int o = 32; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o));
+  if ((threadIdx.x & 63) == 0) atomicMax(longest, len);
 }
 
 __global__ void k_view_fill(int64_t n0, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
@@ -1612,10 +1615,13 @@ void compact_view(const DevCSR& V, DevCSR& out, hipStream_t s) {
     SPPC_HIP(dev_malloc_tmp(&cnt, sizeof(int32_t) * (n0 + 1)));
     SPPC_HIP(dev_malloc_tmp(&bsum, sizeof(int64_t) * (cdiv(n0 + 1, SCAN_BLOCK) + 1)));
     SPPC_HIP(dev_malloc(&out.rp, sizeof(int64_t) * (n0 + 1)));
-    k_view_count<<<cdiv(n0 > 0 ? n0 : 1, 256), 256, 0, s>>>(n0, V.rp, V.rend, cnt);
+    int* const longest = (int*)(bsum + cdiv(n0 + 1, SCAN_BLOCK));  // the last entry, which the scan leaves alone
+    SPPC_HIP(hipMemsetAsync(longest, 0, sizeof(int), s));
+    k_view_count<<<cdiv(n0 > 0 ? n0 : 1, 256), 256, 0, s>>>(n0, V.rp, V.rend, cnt, longest);
     SPPC_LAUNCH_CHECK();
     scan_exclusive_impl(n0, cnt, out.rp, bsum, s);
     int64_t nnz = 0;
+    SPPC_HIP(hipMemcpyAsync(&out.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
     SPPC_HIP(hipMemcpyAsync(&nnz, out.rp + n0, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SPPC_HIP(hipStreamSynchronize(s));
     out.nnz = nnz;
