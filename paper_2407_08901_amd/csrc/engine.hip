@@ -506,8 +506,12 @@ void correct_perturbative(sppc_ctx* c, const double* shifts_host = nullptr) {
   // complement rows: x2 = -b2 / E^(0) with b2 = -W2 (H0 is zero there), eq. sm_first
   complement_rows(n0, n, k, c->Wb, k, sig, c->Psi, k, s);
   // small space: b1 = -W1 + H0hat Psi^(p-1)_1 (eq. exp_seq2 with eq. avoid_SpMV2)
+  // The product takes H0hat as a view with row ends, as setup took H for H Psi^(0): the same kernel, so that the two
+  // sums of a row agree bit by bit and b1 is exactly zero at p = 1.
   gemm_nn(n0, b.m, k, b.Q, b.ldq, c->Acoef, k, c->cx, k, 1.0, 0.0, s);
-  spmm_f64(c->H0, c->cx, k, c->cr, k, k, nullptr, s);
+  DevCSR H0v = c->H0;
+  H0v.rend = c->H0.rp + 1;
+  spmm_f64(H0v, c->cx, k, c->cr, k, k, nullptr, s);
   axpby_block(n0, k, -1.0, c->Wb, k, 1.0, c->cr, k, s);
   small_solve(c, shifts_host ? c->cshift : nullptr);
   if (shifts_host) sync(c);  // the pinned shifts are reused by later steps
