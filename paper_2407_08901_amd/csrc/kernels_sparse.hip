@@ -12,6 +12,7 @@
 #include <string>
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace sppc {
@@ -1131,9 +1132,9 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
     k_pad_copy<XT><<<(unsigned)cdiv(P.n * B, 256), 256, 0, s>>>(P.n, b, X, ldx, xp, B);
     Xc = xp;
   }
-  // Launch shapes, words and values two tiles ahead in all of them: one-wave workgroups, four per CU
-  // (eight for float32 X of width 8), or two-wave workgroups, two (float64 X) or four (float32 X) per
-  // CU.  Measured per product (ms, one-wave / two-wave):
+  // Launch shapes, words and values two tiles ahead in all of them: one-wave workgroups, four per CU (the
+  // exceptions at widths 4 and 8: below), or two-wave workgroups, two (float64 X) or four (float32 X) per CU.
+  // Measured per product (ms, one-wave / two-wave):
   //   n = 7.72M, d = 300:  b = 4: 17.7 / 29.2 (float64 X), 14.0 / 21.1 (float32);
   //                        b = 8: 20.6 / 34.4, 18.5 / 25.5;  b = 16: two-wave 13-15% slower
   //   n = 1.17M, d = 200, float64 X:  b = 4: 1.44 / 1.89;  b = 8: 1.64 / 1.93;  b = 16: 2.16 / 2.09
@@ -1158,19 +1159,46 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
     }
   }
   // Sums over runs of a row's entries where a row has several in a panel (run = their mean): the LDS adds
-  // of the wider products are their bound, and a run costs one set.  Measured (ms, without / with):
+  // of the wider products are their bound, and a run costs one set; a long run also puts the adds of many lanes on
+  // one address.  Measured (ms, without / with):
   //   float32 X  b = 8:   run 1.4 1.54 / 1.42, 2.8 1.55 / 1.44 (n = 1.17M), 3.2 1.51 / 1.32 (772k),
   //                       6.4 0.73 / 0.65 (386k), six one-wave workgroups per CU
   //              b = 16:  1.95 / 1.85, 1.98 / 1.90, 1.77 / 1.69 with four two-wave workgroups per CU; 0.97 /
   //                       0.80 with two four-wave ones (1.93 at run 2.8)
   //   float64 X  b = 8:   1.68 / 1.70, 1.69 / 1.71, 1.64 / 1.61, 0.86 / 0.80
   //              b = 16:  2.17 / 2.38, 2.19 / 2.41, 2.06 / 2.10, 1.06 / 0.95 (three two-wave workgroups)
-  // Up to b = 4 the sums change nothing (+-5%).  Below one entry per row and panel there are no runs.
-  if constexpr (B >= 8) {
+  //   b = 4, float32 X:   run 2.8 1.19 / 1.25, 4.1 0.50 / 0.52, 6.5 0.53 / 0.54, 12 0.66 / 0.58, 20 0.32 / 0.19,
+  //          float64 X:   54 1.37 / 0.53
+  // Below one entry per row and panel there are no runs.
+  //
+  // Workgroups per CU for b = 4 and 8.  At most 4 row blocks per CU leave one-wave workgroups too few waves: two
+  // waves each (n = 150k, d = 200, b = 8: float32 X 0.28 / 0.22, float64 0.30 / 0.27; at 262k 0.38 / 0.31 and 0.36 /
+  // 0.36; b = 4 at 120k 0.135 / 0.128).  Else as many one-wave workgroups as fill their last round best: a round of
+  // a few blocks takes as long as a full one (400k, d = 300, 6.1 blocks per CU: b = 8 with 6 per CU 0.99, with 8
+  // 0.76; float64 X 1.14 and 0.91; b = 4 with 4 per CU 0.74, with 8 0.64).  Beyond 8 blocks per CU the products with
+  // float64 X and of width 4 keep 4, whose gathers stay closer together in the panels (n = 1.17M, d = 60, float64
+  // X: b = 8 with 4 per CU 0.65, with 6 0.81, with 8 0.76).
+  if constexpr (B == 4 || B == 8) {
+    if (!big) {
+      const double x = (double)P.nblocks / panel_cus();  // row blocks per CU
+      const auto fill = [&](int c) { return x / (c * std::ceil(x / c)); };
+      const bool narrow = B == 8 && sizeof(XT) == 4;
+      const bool runs = P.run >= (narrow ? 1.2 : B == 8 ? 4.0 : 8.0);
+      if (x <= (narrow ? 4.0 : B == 8 ? 3.0 : 2.0)) {
+        if (runs) spmm_panel_rounds<B, 2, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
+        else spmm_panel_rounds<B, 2, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
+        return;
+      }
+      int bpc = x <= 8.0 && (fill(4) < 0.85 || (B == 4 && runs)) ? 8 : 4;
+      if (narrow) bpc = fill(6) > fill(8) ? 6 : 8;
+      if (runs) spmm_panel_rounds<B, 1, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
+      else spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
+      return;
+    }
+  }
+  if constexpr (B == 16) {
     if (!big && P.run >= (sizeof(XT) == 4 ? 1.2 : 4.0)) {
-      if constexpr (B == 8)
-        spmm_panel_rounds<B, 1, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 6, s, X64, ldx64);
-      else if constexpr (sizeof(XT) == 8)
+      if constexpr (sizeof(XT) == 8)
         spmm_panel_rounds<B, 2, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 3, s, X64, ldx64);
       else if (P.run >= 4.0)
         spmm_panel_rounds<B, 4, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 2, s, X64, ldx64);
@@ -1180,7 +1208,7 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
     }
   }
   if (big || B <= 8)
-    spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, !big && B == 8 && sizeof(XT) == 4 ? 8 : 4, s, X64, ldx64);
+    spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
   else
     spmm_panel_rounds<B, 2, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, sizeof(XT) == 4 ? 4 : 2, s, X64, ldx64);
 }
