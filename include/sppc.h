@@ -227,9 +227,12 @@ sppc_status sppc_setup(sppc_ctx** out, const sppc_csr* H, const int64_t* level_o
  * Y = H X for the matrix of the context (the paper's cost unit, Sec. IV.C).
  *   X_dev   row-major n x b, float64 (xt = SPPC_F64) or float32 (SPPC_F32)
  *   Y_dev   row-major n x b, float64
- *   b       1..32 (with the column-panel copy of H, widths above 16 go in column blocks of 16 and the rest)
+ *   b       1..32 (with the column-panel copy of H, widths above 16 go in column blocks of 16 and the rest where the
+ *           rows hold enough entries, else row by row)
  * float64 X uses the float64 values; float32 X uses the float32 values with
  * float32 products accumulated in float64.  Asynchronous on the context stream.
+ * Through the column-panel copy the order of a row's float64 sums depends on scheduling (also for widths
+ * above 16), so two calls can differ in the last bits; row by row it is fixed.
  */
 sppc_status sppc_spmm(sppc_ctx* ctx, const void* X_dev, sppc_dtype xt, double* Y_dev, int b);
 
@@ -260,8 +263,9 @@ sppc_status sppc_spmm_upper(const sppc_csr* H, const void* X_dev, sppc_dtype xt,
  * its kernels read (b in {1, 2, 4, 8, 16} columns per row, 16-byte aligned), X is copied to a row stride
  * B = 1, 2, 4, 8 or 16 in the library's static device scratch array (32 MiB per device, held until the
  * process ends) instead of the context's buffer; n * B * sizeof(X element) beyond 32 MiB is
- * rejected with SPPC_E_ARG (b > 16: the row-wise kernel, which needs no copy, takes the call).  Every call on one device shares that array and it keeps the last
- * call's contents: calls that overlap on one device (several streams or threads) race.
+ * rejected with SPPC_E_ARG (b > 16: the row-wise kernel, which needs no copy, takes the call).  Every
+ * call on one device shares that array and it keeps the last call's contents: calls that overlap on one
+ * device (several streams or threads) race.
  * Arguments, layout and errors as sppc_spmm.
  */
 sppc_status sppc_spmm_noalloc(sppc_ctx* ctx, const void* X_dev, sppc_dtype xt, double* Y_dev, int b);

@@ -1747,12 +1747,16 @@ void release_panel(PanelH& p) {
   p = PanelH{};
 }
 
-// Products that take the panel copy: no shift; widths 17..32 only where the copy of X they need
-// fits the given scratch (the row-wise kernel needs none).
+// Products that take the panel copy: no shift; widths 17..32 only where the copy of X they need fits the given
+// scratch (the row-wise kernel needs none) and the rows hold enough entries to pay for it and for the passes over
+// the row sums: from 48 entries a row with float64 X (us, row-wise / panel, b = 32: 6 entries n = 150k 59 / 109, 20
+// entries n = 400k 302 / 390, 45 entries n = 1.2M 1883 / 1983, 60 entries n = 1.2M 1.07x, n = 400k 1.19x, 300 entries
+// 1.57x; the odd widths gain more), from 16 with float32 X (b = 27: 6 entries n = 1.2M 546 / 604, 20 entries 1.01 to 1.56x).
 static bool use_panel(const DevCSR& H, int b, const double* shift, const void* stage, size_t stage_bytes,
                       size_t elem) {
   if (!H.panel || shift || b < 1 || b > 32 || H.n <= 0) return false;
-  return b <= 16 || !stage || (size_t)H.n * 16 * elem <= stage_bytes;
+  if (b <= 16) return true;
+  return H.nnz >= (elem == 8 ? 48 : 16) * H.n && (!stage || (size_t)H.n * 16 * elem <= stage_bytes);
 }
 
 void spmm_f64(const DevCSR& H, const double* X, int64_t ldx, double* Y, int64_t ldy, int b,

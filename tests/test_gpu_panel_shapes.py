@@ -1,5 +1,6 @@
 """The panel product's launch shapes of widths 4 and 8 by the row blocks per compute unit (one or two waves, a
-full or a nearly empty last round), with and without sums over runs, against SciPy in float64."""
+full or a nearly empty last round), with and without sums over runs, and widths above 16 at 26 entries a row (row
+by row with float64 X, column blocks with float32), against SciPy in float64."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,7 @@ def test_panel_shapes(P, n):
     for pw in (65536, 4096):  # 6 to 13 entries per row and panel, and below one
         ctx = P.sppc_setup(rp, col, val, A.level_offsets, 1, 4,
                            P.sppc_default_opts(panel_width=pw, precision=P.SPPC_PREC_MIXED, maxiter=0, p_switch=0, m_max=8))
-        for b in (4, 7, 8):
+        for b in (4, 7, 8, 20, 27):
             Xh = rng.standard_normal((n, b)).astype(np.float32).astype(np.float64)
             ref, scale = H @ Xh, aH @ np.abs(Xh)
             # float64: rounding of the sums; float32 X: one rounding of each product
