@@ -353,7 +353,7 @@ __global__ void k_diag(int64_t n, const int64_t* __restrict__ rp, const int32_t*
 // group read the B contiguous entries of the gathered row of X (one 8*B-byte segment)
 // and accumulate into one float64 register per lane.  The groups are summed with
 // cross-lane shuffles at the end of the row.
-template <int B, typename VT, typename XT>
+template <int B, bool FULL, typename VT, typename XT>
 __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restrict__ rp,
                                               const int64_t* __restrict__ rend,
                                               const int32_t* __restrict__ col,
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restri
                                               const double* __restrict__ shift, double ea, double ec,
                                               double eb, const double* __restrict__ Zo, int64_t ldz,
                                               const double* __restrict__ dg, const double* __restrict__ X64,
-                                              int64_t ldx64, int full) {
+                                              int64_t ldx64) {
   constexpr int G = 64 / B;
   const int lane = threadIdx.x & 63;
   const int g = lane / B;
@@ -385,13 +385,10 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restri
       if constexpr (sizeof(XT) == 4) return acc + (double)(vv * xv);  // float32 product, float64 accumulation
       else return fma((double)vv, (double)xv, acc);
     };
-    // A full window has no bounds checks and its gathers are issued together; lanes beyond b repeat column 0.
+    // FULL: a full window has no bounds checks and its gathers are issued together; lanes beyond b repeat column 0.
     // us, before / after, n = 117k: float32 X b = 4 164 / 155, 8 227 / 166, 16 411 / 225, 32 734 / 339; float64
-    // X b = 6 260 / 240, 27 879 / 835; n = 27.5k, float32 X 21.0 / 19.5, 28.5 / 23.0, 42 / 30, 77 / 49.  The
-    // narrower widths are bound by the line rate of the gathers and lose up to 6% (float64 X b = 2 163 / 172,
-    // b = 3 187 / 195); so do float64 X of width 5 to 8 from 200000 rows, where X is far beyond L2 and more gathers
-    // per wave spread the waves over its columns (n = 281k, b = 6 818 / 862): full = 0 there.
-    if (B >= (sizeof(XT) == 4 ? 4 : 8) && full && cnt == 64) {
+    // X b = 6 260 / 240, 27 879 / 835; n = 27.5k, float32 X 21.0 / 19.5, 28.5 / 23.0, 42 / 30, 77 / 49.
+    if (FULL && cnt == 64) {
       const XT* xc = X + (colok ? c : 0);
 #pragma unroll
       for (int s0 = 0; s0 < 64; s0 += G) {
@@ -581,23 +578,34 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   if (H.n == 0) return;
   const int64_t grid = cdiv(H.n, 4);
   if constexpr (sizeof(XT) == 8) {
-    // Plain products of a whole matrix: width 4; widths 8 and 16 while X (n < 250000, n <= 65536: 16 and 8 MB) is not
-    // far beyond L2 (b = 8: 216k rows 547 / 524 us, from 281k on even within the 3% that two processes differ by).
-    if ((b == 4 || (b == 8 && H.n < 250000) || (b == 16 && H.n <= 65536)) && !shift && !Zo && !dg && !H.rend &&
-        ldx % 2 == 0 && ldx < (1 << 30) && ((uintptr_t)X & 15) == 0) {
-      // Four rows per wave where X is beyond L2 (from 100000 rows of 64 bytes, 200000 of 32), and 32 KB of LDS per
-      // workgroup, which leave room for 5 on a CU (b = 4, one row / four: 216k rows 357 / 354, 281k 571 / 531).
-      const int64_t g4 = cdiv(H.n, 16);
-      if (b == 4 && H.n >= 200000 && H.n < (1 << 29))
-        k_spmm_rows<2, 4, VT><<<g4, 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+    // Plain products of a whole matrix (k_spmm_rows), by the bytes of X against the 4 MB of an L2 and the entries of
+    // a row (us, before / after).  One row per wave while X is near one L2: width 4 from 40 entries a row (6 entries
+    // n = 30k 8.0 / 9.7, 20 entries 8.9 / 9.8, n = 90k 1.08x, 60 entries 1.17x), width 8 from 16 (6 entries 1.09x
+    // slower, 20 entries n = 30k 1.09x, 90k 1.20x), width 16 always (1.01 to 1.22x).  Four rows per wave, and 32 KB of
+    // LDS per workgroup, which leave room for 5 on a CU, where X is beyond it: width 8 up to 4 L2 (216k rows of 196
+    // entries 547 / 524, from 281k on even), width 4 without end (one row / four: 216k rows 357 / 354, 281k 571 / 531),
+    // both from 100 entries (20 entries: 150k b = 8 63 / 69, 400k b = 4 136 / 149; 60 entries 3 to 5% slower).
+    constexpr int64_t L2 = (int64_t)4 << 20;
+    const int64_t xb = H.n * ldx * 8, deg = H.nnz / H.n;
+    const bool plain = !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 && ldx < (1 << 30) && ((uintptr_t)X & 15) == 0;
+    const bool one = 5 * xb <= 8 * L2;
+    int rows = 0;  // rows per wave
+    if (plain && b == 4) rows = one ? (deg >= 40 ? 1 : 0) : (deg >= 100 && H.n < (1 << 29) ? 4 : 0);
+    if (plain && b == 8) rows = one ? (deg >= 16 ? 1 : 0) : (deg >= 100 && xb <= 4 * L2 ? 4 : 0);
+    if (plain && b == 16) rows = xb <= 2 * L2 ? 1 : 0;
+    if (rows) {
+      const int64_t g = cdiv(H.n, 4 * rows);
+      const size_t lds = rows == 4 ? 32768 : 0;
+      if (b == 4 && rows == 4)
+        k_spmm_rows<2, 4, VT><<<g, 256, lds, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else if (b == 4)
-        k_spmm_rows<2, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
-      else if (b == 8 && H.n >= 100000)
-        k_spmm_rows<4, 4, VT><<<g4, 256, 32768, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+        k_spmm_rows<2, 1, VT><<<g, 256, lds, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+      else if (b == 8 && rows == 4)
+        k_spmm_rows<4, 4, VT><<<g, 256, lds, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else if (b == 8)
-        k_spmm_rows<4, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+        k_spmm_rows<4, 1, VT><<<g, 256, lds, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       else
-        k_spmm_rows<8, 1, VT><<<grid, 256, 0, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
+        k_spmm_rows<8, 1, VT><<<g, 256, lds, s>>>(H.n, H.rp, H.col, val, X, ldx, Y, ldy);
       SPPC_LAUNCH_CHECK();
       return;
     }
@@ -612,18 +620,34 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
       return;
     }
   }
-  const int full = sizeof(XT) == 4 || b > 8 || H.n < 200000;
-#define SPPC_SPMM_CASE(BB)                                                                        \
-  k_spmm<BB, VT, XT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec, \
-                                          eb, Zo, ldz, dg, X64, ldx64, full);                               \
+  // Full windows (k_spmm's FULL) need rows of about a window (20 entries: the test for them alone costs 2 to 5%).
+  // The narrower widths are bound by the line rate of the gathers and lose up to 6% (float64 X b = 2 163 / 172 us, b = 3
+  // 187 / 195); so do float64 X of width 5 to 8 beyond two L2, where more gathers per wave spread the waves over its
+  // columns (X of 7.2 MB 0.98 to 1.07x, 8.4 MB of 500 entries a row 866 / 968; n = 281k, b = 6 818 / 862).
+  const bool full = (H.rend || H.nnz >= 48 * H.n) &&
+                    (sizeof(XT) == 4 ? b > 2 : b > 8 || (b > 4 && H.n * ldx * 8 <= (int64_t)8 << 20));
+#define SPPC_SPMM_CASE(BB, F)                                                                        \
+  k_spmm<BB, F, VT, XT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec, \
+                                             eb, Zo, ldz, dg, X64, ldx64);                                 \
   break;
-  switch (b <= 1 ? 1 : b <= 2 ? 2 : b <= 4 ? 4 : b <= 8 ? 8 : b <= 16 ? 16 : 32) {
-    case 1: SPPC_SPMM_CASE(1)
-    case 2: SPPC_SPMM_CASE(2)
-    case 4: SPPC_SPMM_CASE(4)
-    case 8: SPPC_SPMM_CASE(8)
-    case 16: SPPC_SPMM_CASE(16)
-    default: SPPC_SPMM_CASE(32)
+  const int w = b <= 1 ? 1 : b <= 2 ? 2 : b <= 4 ? 4 : b <= 8 ? 8 : b <= 16 ? 16 : 32;
+  if (full) {
+    switch (w) {
+      case 4:
+        if constexpr (sizeof(XT) == 4) { SPPC_SPMM_CASE(4, true) }
+      case 8: SPPC_SPMM_CASE(8, true)
+      case 16: SPPC_SPMM_CASE(16, true)
+      default: SPPC_SPMM_CASE(32, true)
+    }
+  } else {
+    switch (w) {
+      case 1: SPPC_SPMM_CASE(1, false)
+      case 2: SPPC_SPMM_CASE(2, false)
+      case 4: SPPC_SPMM_CASE(4, false)
+      case 8: SPPC_SPMM_CASE(8, false)
+      case 16: SPPC_SPMM_CASE(16, false)
+      default: SPPC_SPMM_CASE(32, false)
+    }
   }
 #undef SPPC_SPMM_CASE
   SPPC_LAUNCH_CHECK();
@@ -1168,28 +1192,30 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
   //   float64 X  b = 8:   1.68 / 1.70, 1.69 / 1.71, 1.64 / 1.61, 0.86 / 0.80
   //              b = 16:  2.17 / 2.38, 2.19 / 2.41, 2.06 / 2.10, 1.06 / 0.95 (three two-wave workgroups)
   //   b = 4, float32 X:   run 2.8 1.19 / 1.25, 4.1 0.50 / 0.52, 6.5 0.53 / 0.54, 12 0.66 / 0.58, 20 0.32 / 0.19,
-  //          float64 X:   54 1.37 / 0.53
+  //          float64 X:   54 1.37 / 0.53, 4.1 0.59 / 0.58
   // Below one entry per row and panel there are no runs.
   //
-  // Workgroups per CU for b = 4 and 8.  At most 4 row blocks per CU leave one-wave workgroups too few waves: two
-  // waves each (n = 150k, d = 200, b = 8: float32 X 0.28 / 0.22, float64 0.30 / 0.27; at 262k 0.38 / 0.31 and 0.36 /
-  // 0.36; b = 4 at 120k 0.135 / 0.128).  Else as many one-wave workgroups as fill their last round best: a round of
-  // a few blocks takes as long as a full one (400k, d = 300, 6.1 blocks per CU: b = 8 with 6 per CU 0.99, with 8
-  // 0.76; float64 X 1.14 and 0.91; b = 4 with 4 per CU 0.74, with 8 0.64).  Beyond 8 blocks per CU the products with
-  // float64 X and of width 4 keep 4, whose gathers stay closer together in the panels (n = 1.17M, d = 60, float64
-  // X: b = 8 with 4 per CU 0.65, with 6 0.81, with 8 0.76).
+  // Workgroups per CU for b = 4 and 8.  At most 3 row blocks per CU (float32 X of width 8: 4) leave one-wave
+  // workgroups too few waves: two waves each (n = 150k, d = 200, b = 8: float32 X 0.28 / 0.22, float64 0.30 / 0.27; at
+  // 262k 0.38 / 0.31 and 0.36 / 0.36; b = 4 at 120k 0.135 / 0.128, at 150k with 6 entries a row 0.0126 / 0.0102).  Else
+  // as many one-wave workgroups as fill their last round best: a round of a few blocks takes as long as a full one
+  // (400k, d = 300, 6.1 blocks per CU: b = 8 with 6 per CU 0.99, with 8 0.76; float64 X 1.14 and 0.91; b = 4 with 4 per
+  // CU 0.74, with 8 0.64).  Beyond 8 blocks per CU the products with float64 X and of width 4 keep 4, whose gathers
+  // stay closer together in the panels (n = 1.17M, d = 60, float64 X: b = 8 with 4 per CU 0.65, with 6 0.81, with 8
+  // 0.76), unless a row has few entries (6 at n = 1.2M: 0.19 / 0.165 with 8, 20: 0.37 / 0.38).
   if constexpr (B == 4 || B == 8) {
     if (!big) {
       const double x = (double)P.nblocks / panel_cus();  // row blocks per CU
       const auto fill = [&](int c) { return x / (c * std::ceil(x / c)); };
       const bool narrow = B == 8 && sizeof(XT) == 4;
-      const bool runs = P.run >= (narrow ? 1.2 : B == 8 ? 4.0 : 8.0);
-      if (x <= (narrow ? 4.0 : B == 8 ? 3.0 : 2.0)) {
+      const bool runs = P.run >= (narrow ? 1.2 : sizeof(XT) == 8 ? 4.0 : 8.0);
+      if (x <= (narrow ? 4.0 : 3.0)) {
         if (runs) spmm_panel_rounds<B, 2, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
         else spmm_panel_rounds<B, 2, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, 4, s, X64, ldx64);
         return;
       }
-      int bpc = x <= 8.0 && (fill(4) < 0.85 || (B == 4 && runs)) ? 8 : 4;
+      const bool few = P.run * P.P < 16.0;  // entries of a row
+      int bpc = few || (x <= 8.0 && (fill(4) < 0.85 || (B == 4 && runs))) ? 8 : 4;
       if (narrow) bpc = fill(6) > fill(8) ? 6 : 8;
       if (runs) spmm_panel_rounds<B, 1, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
       else spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
