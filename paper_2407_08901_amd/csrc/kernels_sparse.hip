@@ -1200,9 +1200,10 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
   // 262k 0.38 / 0.31 and 0.36 / 0.36; b = 4 at 120k 0.135 / 0.128, at 150k with 6 entries a row 0.0126 / 0.0102).  Else
   // as many one-wave workgroups as fill their last round best: a round of a few blocks takes as long as a full one
   // (400k, d = 300, 6.1 blocks per CU: b = 8 with 6 per CU 0.99, with 8 0.76; float64 X 1.14 and 0.91; b = 4 with 4 per
-  // CU 0.74, with 8 0.64).  Beyond 8 blocks per CU the products with float64 X and of width 4 keep 4, whose gathers
-  // stay closer together in the panels (n = 1.17M, d = 60, float64 X: b = 8 with 4 per CU 0.65, with 6 0.81, with 8
-  // 0.76), unless a row has few entries (6 at n = 1.2M: 0.19 / 0.165 with 8, 20: 0.37 / 0.38).
+  // CU 0.74, with 8 0.64).  Beyond 8 blocks per CU, and below it where a second round of 4 is more than half full
+  // (6.6 at n = 430k, d = 180, float64 X, b = 4: 0.47 with 4, 0.50 with 8), the products with float64 X and of width 4
+  // keep 4, whose gathers stay closer together in the panels (n = 1.17M, d = 60, float64 X: b = 8 with 4 per CU 0.65,
+  // with 6 0.81, with 8 0.76), unless a row has few entries (6 at n = 1.2M: 0.19 / 0.165 with 8, 20: 0.37 / 0.38).
   if constexpr (B == 4 || B == 8) {
     if (!big) {
       const double x = (double)P.nblocks / panel_cus();  // row blocks per CU
@@ -1215,7 +1216,7 @@ void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, doub
         return;
       }
       const bool few = P.run * P.P < 16.0;  // entries of a row
-      int bpc = few || (x <= 8.0 && (fill(4) < 0.85 || (B == 4 && runs))) ? 8 : 4;
+      int bpc = few || (x <= 8.0 && fill(4) < 0.78) ? 8 : 4;
       if (narrow) bpc = fill(6) > fill(8) ? 6 : 8;
       if (runs) spmm_panel_rounds<B, 1, 2, true, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
       else spmm_panel_rounds<B, 1, 2, false, VT, XT>(P, val, Xc, Y, ldy, b, bpc, s, X64, ldx64);
