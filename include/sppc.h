@@ -231,6 +231,7 @@ sppc_status sppc_setup(sppc_ctx** out, const sppc_csr* H, const int64_t* level_o
  *           rows hold enough entries, else row by row)
  * float64 X uses the float64 values; float32 X uses the float32 values with
  * float32 products accumulated in float64.  Asynchronous on the context stream.
+ * Y may overlap X only where the column-panel copy of H takes a call with b <= 16 (X is then copied first).
  * Through the column-panel copy the order of a row's float64 sums depends on scheduling (also for widths
  * above 16), so two calls can differ in the last bits; row by row it is fixed.
  */

@@ -1137,13 +1137,16 @@ inline SpmvShape spmv_shape(const PanelH& P, int64_t elem, int cus) {
   return best;
 }
 
-// X is read from a copy with row stride B when the caller's X is not in that layout: the copy goes
-// to `stage` (stage_bytes long) when given, else to the panel's own buffer.
+// X is read from a copy with row stride B when the caller's X is not in that layout, or when Y overlaps it (workgroups
+// that are done write rows that others still gather): the copy goes to `stage` (stage_bytes long) when given, else to
+// the panel's own buffer.
 template <int B, typename VT, typename XT>
 void spmm_panel_b(const PanelH& P, const VT* val, const XT* X, int64_t ldx, double* Y, int64_t ldy, int b,
                   hipStream_t s, const double* X64, int64_t ldx64, void* stage, size_t stage_bytes) {
   const XT* Xc = X;
-  if (ldx != B || ((uintptr_t)X & 15) != 0) {
+  const bool overlap = (uintptr_t)X < (uintptr_t)(Y + (P.n - 1) * ldy + b) &&
+                       (uintptr_t)Y < (uintptr_t)(X + (P.n - 1) * ldx + b);
+  if (ldx != B || ((uintptr_t)X & 15) != 0 || overlap) {
     XT* xp = (XT*)P.xpad;
     if (stage) {
       const size_t need = (size_t)P.n * B * sizeof(XT);
