@@ -98,7 +98,7 @@ struct DevCSR {
   double* val64 = nullptr;     // float64 values (nullptr when val32 is exact and enough)
   float* val32 = nullptr;      // float32 values
   const PanelH* panel = nullptr;  // optional panel copy used by the plain products
-  int longest = 0;             // entries of the longest row (compact_view only)
+  int longest = 0;             // entries of the longest row (compact_view, up to 1024 rows)
 };
 
 // Setup: build the full CSR from the upper triangle.  Returns nnz of the full matrix.

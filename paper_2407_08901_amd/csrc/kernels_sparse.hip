@@ -655,12 +655,23 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
 
 // rows [0, n0) restricted to columns < n0 (the row ends of the view), copied contiguously
 __global__ void k_view_count(int64_t n0, const int64_t* __restrict__ rp, const int64_t* __restrict__ rend,
-                             int32_t* __restrict__ cnt, int* __restrict__ longest) {
+                             int32_t* __restrict__ cnt) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int len = 0;
-  if (i < n0) cnt[i] = len = (int32_t)(rend[i] - rp[i]);
+  if (i < n0) cnt[i] = (int32_t)(rend[i] - rp[i]);
+}
+
+// the largest of n0 <= 1024 counts; one workgroup
+__global__ __launch_bounds__(1024) void k_longest(int64_t n0, const int32_t* __restrict__ cnt,
+                                                  int64_t* __restrict__ longest) {
+  __shared__ int sh[16];
+  int len = threadIdx.x < n0 ? cnt[threadIdx.x] : 0;
   for (int o = 32; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o));
-  if ((threadIdx.x & 63) == 0) atomicMax(longest, len);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = len;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) len = max(len, sh[w]);
+    *longest = len;
+  }
 }
 
 __global__ void k_view_fill(int64_t n0, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
@@ -1672,16 +1683,16 @@ void compact_view(const DevCSR& V, DevCSR& out, hipStream_t s) {
     out.n = n0;
     SPPC_HIP(dev_malloc_tmp(&cnt, sizeof(int32_t) * (n0 + 1)));
     SPPC_HIP(dev_malloc_tmp(&bsum, sizeof(int64_t) * (cdiv(n0 + 1, SCAN_BLOCK) + 1)));
-    SPPC_HIP(dev_malloc(&out.rp, sizeof(int64_t) * (n0 + 1)));
-    int* const longest = (int*)(bsum + cdiv(n0 + 1, SCAN_BLOCK));  // the last entry, which the scan leaves alone
-    SPPC_HIP(hipMemsetAsync(longest, 0, sizeof(int), s));
-    k_view_count<<<cdiv(n0 > 0 ? n0 : 1, 256), 256, 0, s>>>(n0, V.rp, V.rend, cnt, longest);
+    SPPC_HIP(dev_malloc(&out.rp, sizeof(int64_t) * (n0 + 2)));  // the longest row's length after the row bounds
+    k_view_count<<<cdiv(n0 > 0 ? n0 : 1, 256), 256, 0, s>>>(n0, V.rp, V.rend, cnt);
+    if (n0 <= 1024) k_longest<<<1, 1024, 0, s>>>(n0, cnt, out.rp + n0 + 1);
     SPPC_LAUNCH_CHECK();
     scan_exclusive_impl(n0, cnt, out.rp, bsum, s);
-    int64_t nnz = 0;
-    SPPC_HIP(hipMemcpyAsync(&out.longest, longest, sizeof(int), hipMemcpyDeviceToHost, s));
-    SPPC_HIP(hipMemcpyAsync(&nnz, out.rp + n0, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    int64_t ends[2] = {0, 0};
+    SPPC_HIP(hipMemcpyAsync(ends, out.rp + n0, sizeof(int64_t) * (n0 <= 1024 ? 2 : 1), hipMemcpyDeviceToHost, s));
     SPPC_HIP(hipStreamSynchronize(s));
+    const int64_t nnz = ends[0];
+    out.longest = (int)ends[1];
     out.nnz = nnz;
     SPPC_HIP(dev_malloc(&out.col, sizeof(int32_t) * (nnz > 0 ? nnz : 1)));
     if (V.val64) SPPC_HIP(dev_malloc(&out.val64, sizeof(double) * (nnz > 0 ? nnz : 1)));
@@ -1851,7 +1862,7 @@ BuildBytes panel_bytes(int64_t n, int64_t nnz_full, bool v64, bool v32) {
 BuildBytes view_bytes(int64_t n0, int64_t nnz0, bool v64, bool v32) {
   BuildBytes b;
   const int64_t z = std::max<int64_t>(nnz0, 1);
-  b.persist = ws_bytes(8 * (n0 + 1)) + ws_bytes(4 * z) + (v64 ? ws_bytes(8 * z) : 0) + (v32 ? ws_bytes(4 * z) : 0);
+  b.persist = ws_bytes(8 * (n0 + 2)) + ws_bytes(4 * z) + (v64 ? ws_bytes(8 * z) : 0) + (v32 ? ws_bytes(4 * z) : 0);
   b.temp = ws_bytes(4 * (n0 + 1)) + ws_bytes(8 * (cdiv(n0 + 1, SCAN_BLOCK) + 1));
   return b;
 }
