@@ -622,10 +622,10 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   }
   // Full windows (k_spmm's FULL) need rows of about a window (20 entries: the test for them alone costs 2 to 5%).
   // The narrower widths are bound by the line rate of the gathers and lose up to 6% (float64 X b = 2 163 / 172 us, b = 3
-  // 187 / 195); so do float64 X of width 5 to 8 beyond two L2, where more gathers per wave spread the waves over its
-  // columns (X of 7.2 MB 0.98 to 1.07x, 8.4 MB of 500 entries a row 866 / 968; n = 281k, b = 6 818 / 862).
+  // 187 / 195); so do float64 X of width 5 to 8 beyond 1.6 L2, where more gathers per wave spread the waves over its
+  // columns (X of 6 MB 1.05x, 7.2 MB 0.98 to 1.07x, 8.2 MB 547 / 562, 8.4 MB of 500 entries a row 866 / 968).
   const bool full = (H.rend || H.nnz >= 48 * H.n) &&
-                    (sizeof(XT) == 4 ? b > 2 : b > 8 || (b > 4 && H.n * ldx * 8 <= (int64_t)8 << 20));
+                    (sizeof(XT) == 4 ? b > 2 : b > 8 || (b > 4 && 5 * H.n * ldx <= (int64_t)4 << 20));
 #define SPPC_SPMM_CASE(BB, F)                                                                        \
   k_spmm<BB, F, VT, XT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec, \
                                              eb, Zo, ldz, dg, X64, ldx64);                                 \
