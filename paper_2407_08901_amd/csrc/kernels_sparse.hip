@@ -990,9 +990,9 @@ void spmm_panel_rounds(const PanelH& P, const VT* val, const XT* Xc, double* Y, 
 //
 // A gathered element of a single column still costs the line rate of a row (0.96 ns per CU from L2).  Here
 // a workgroup brings each panel of X to LDS (global loads straight to LDS, 1 KB per wave), and its waves take a
-// row block each: a wave goes through the stream of its block, 4 consecutive entries per lane and up to two
-// batches of 1024 entries ahead, and joins the workgroup's next panel when an entry lies beyond this one, so
-// every wave passes every panel once.  X is read once per workgroup instead of once per entry.  Entries of one
+// row block each: a wave goes through the stream of its block, 4 consecutive entries per lane and one batch
+// of 1024 entries ahead, and joins the workgroup's next panel when an entry lies beyond this one (the wait for the
+// panel's loads straight to LDS also waits for the batch ahead), so every wave passes every panel once.  X is read once per workgroup instead of once per entry.  Entries of one
 // row are summed in the lane before their LDS add: with one entry per lane the adds of neighbouring lanes to
 // one row took 60% of the time.  What bounds it now: the latency of a batch per panel, then HBM (n = 772k
 // 4.7 TB/s).  us, gathers from L2 / this:
