@@ -314,7 +314,7 @@ void mpnn_run(const DevCSR& H, const double* diag, const double* lev, const doub
               const double* theta_dev, const double* E, double* T_out, double* grad_out, double* loss_dev,
               double* work, const MpnnBasis* basis, hipStream_t s, bool project = true);
 void mpnn_adam(float* w, float* m, float* v, const double* g, float lr, int step, float* wq, hipStream_t s);
-void mpnn_round_bf16(int cnt, const float* w, float* wq, double* wd, hipStream_t s);
+void mpnn_round_bf16(int cnt, const float* w, float* wq, hipStream_t s);
 // weights (289) and theta (S) from pinned host memory: w64 as they are, or w32 rounded to bfloat16
 void mpnn_inputs(int S, const float* w_host, const double* th_host, float* w32, double* w64, double* th,
                  hipStream_t s);

@@ -1735,7 +1735,7 @@ sppc_status sppc_mpnn_set_weights(sppc_ctx* c, const float* w_host) {
     for (int i = 0; i < SPPC_MPNN_NPARAM; ++i) finite = finite && std::isfinite(w_host[i]);
     c->mp_invalid = !finite;  // every pair then takes the diagonal step
     SPPC_HIP(hipMemcpy(c->mp_w, w_host, sizeof(float) * SPPC_MPNN_NPARAM, hipMemcpyHostToDevice));
-    mpnn_round_bf16(SPPC_MPNN_NPARAM, c->mp_w, c->mp_wq, nullptr, c->s);
+    mpnn_round_bf16(SPPC_MPNN_NPARAM, c->mp_w, c->mp_wq, c->s);
     sync(c);
     c->mp_have_w = true;
     c->mp_fallback.assign(c->k, 0);
@@ -1794,7 +1794,7 @@ sppc_status sppc_mpnn_train_step(sppc_ctx* c, float* state_dev, int S, const dou
     float* v = mo + SPPC_MPNN_NPARAM;
     float* wq = v + SPPC_MPNN_NPARAM;
     upload_theta(c, theta_host, S);
-    mpnn_round_bf16(SPPC_MPNN_NPARAM, w, wq, nullptr, s);
+    mpnn_round_bf16(SPPC_MPNN_NPARAM, w, wq, s);
     mpnn_run<float>(c->H, c->diag, c->mp_lev, c->mp_Ad, c->mp_A1, c->mp_Al, wq, S, R_dev, S, X_dev, S, c->mp_th,
                     E_dev, nullptr, c->mp_grad, c->mp_loss, c->mp_work, bp, s);
     mpnn_adam(w, mo, v, c->mp_grad, lr, step, wq, s);

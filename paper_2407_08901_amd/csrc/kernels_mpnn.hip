@@ -294,6 +294,13 @@ __global__ void k_sum_parts(int64_t nb, const double* __restrict__ part, double*
   if (lane == 0) g[i] = s;
 }
 
+// rounded to bfloat16 (nearest even) and back
+__device__ inline float round_bf16(float w) {
+  uint32_t bits = __float_as_uint(w);
+  bits += 0x7FFFu + ((bits >> 16) & 1u);
+  return __uint_as_float(bits & 0xFFFF0000u);
+}
+
 // Adam on the float32 master weights; the network uses their bfloat16 rounding
 __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
                        const double* __restrict__ g, float lr, float b1, float b2, float eps, int step,
@@ -306,24 +313,12 @@ __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __re
   const float mh = m[i] / (1.f - powf(b1, (float)step));
   const float vh = v[i] / (1.f - powf(b2, (float)step));
   w[i] -= lr * mh / (sqrtf(vh) + eps);
-  if (wq) {
-    // round to bfloat16 (nearest even) and back
-    uint32_t bits = __float_as_uint(w[i]);
-    const uint32_t lsb = (bits >> 16) & 1u;
-    bits += 0x7FFFu + lsb;
-    wq[i] = __uint_as_float(bits & 0xFFFF0000u);
-  }
+  if (wq) wq[i] = round_bf16(w[i]);
 }
 
-__global__ void k_round_bf16(int cnt, const float* __restrict__ w, float* __restrict__ wq, double* __restrict__ wd) {
+__global__ void k_round_bf16(int cnt, const float* __restrict__ w, float* __restrict__ wq) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= cnt) return;
-  uint32_t bits = __float_as_uint(w[i]);
-  const uint32_t lsb = (bits >> 16) & 1u;
-  bits += 0x7FFFu + lsb;
-  const float q = __uint_as_float(bits & 0xFFFF0000u);
-  if (wq) wq[i] = q;
-  if (wd) wd[i] = (double)q;
+  if (i < cnt) wq[i] = round_bf16(w[i]);
 }
 
 // Weights and theta of one evaluation from the caller's pinned host copy (1.2 KB: two copies and their
@@ -334,14 +329,8 @@ __global__ __launch_bounds__(320) void k_mpnn_inputs(int S, const float* __restr
                                                      double* __restrict__ th) {
   const int i = threadIdx.x;
   if (i < NPAR) {
-    if constexpr (sizeof(T) == 4) {
-      uint32_t bits = __float_as_uint(w_host[i]);
-      const uint32_t lsb = (bits >> 16) & 1u;
-      bits += 0x7FFFu + lsb;
-      w[i] = __uint_as_float(bits & 0xFFFF0000u);
-    } else {
-      w[i] = (double)w_host[i];
-    }
+    if constexpr (sizeof(T) == 4) w[i] = round_bf16(w_host[i]);
+    else w[i] = (double)w_host[i];
   }
   if (i < S) th[i] = th_host[i];
 }
@@ -513,8 +502,8 @@ void mpnn_inputs(int S, const float* w_host, const double* th_host, float* w32, 
   SPPC_LAUNCH_CHECK();
 }
 
-void mpnn_round_bf16(int cnt, const float* w, float* wq, double* wd, hipStream_t s) {
-  k_round_bf16<<<cdiv(cnt, 256), 256, 0, s>>>(cnt, w, wq, wd);
+void mpnn_round_bf16(int cnt, const float* w, float* wq, hipStream_t s) {
+  k_round_bf16<<<cdiv(cnt, 256), 256, 0, s>>>(cnt, w, wq);
   SPPC_LAUNCH_CHECK();
 }
 
