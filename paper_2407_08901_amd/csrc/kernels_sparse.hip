@@ -577,6 +577,9 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   if (b < 1 || b > 32) throw Error(1, "spmm: block width must be 1..32");
   if (H.n == 0) return;
   const int64_t grid = cdiv(H.n, 4);
+  // What the gathers touch of X: its rows as they are, or the 128-byte lines they lie in when they are apart.
+  constexpr int64_t L2 = (int64_t)4 << 20;
+  const int64_t xb = H.n * (ldx == b ? b * (int64_t)sizeof(XT) : cdiv(b * (int64_t)sizeof(XT), 128) * 128);
   if constexpr (sizeof(XT) == 8) {
     // Plain products of a whole matrix (k_spmm_rows), by the bytes of X against the 4 MB of an L2 and the entries of
     // a row (us, before / after).  One row per wave while X is near one L2: width 4 from 40 entries a row (6 entries
@@ -585,8 +588,7 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
     // LDS per workgroup, which leave room for 5 on a CU, where X is beyond it: width 8 up to 4 L2 (216k rows of 196
     // entries 547 / 524, from 281k on even), width 4 without end (one row / four: 216k rows 357 / 354, 281k 571 / 531),
     // both from 100 entries (20 entries: 150k b = 8 63 / 69, 400k b = 4 136 / 149; 60 entries 3 to 5% slower).
-    constexpr int64_t L2 = (int64_t)4 << 20;
-    const int64_t xb = H.n * ldx * 8, deg = H.nnz / H.n;
+    const int64_t deg = H.nnz / H.n;
     const bool plain = !shift && !Zo && !dg && !H.rend && ldx % 2 == 0 && ldx < (1 << 30) && ((uintptr_t)X & 15) == 0;
     const bool one = 5 * xb <= 8 * L2;
     int rows = 0;  // rows per wave
@@ -625,7 +627,7 @@ void launch_spmm(const DevCSR& H, const VT* val, const XT* X, int64_t ldx, doubl
   // 187 / 195); so do float64 X of width 5 to 8 beyond 1.6 L2, where more gathers per wave spread the waves over its
   // columns (X of 6 MB 1.05x, 7.2 MB 0.98 to 1.07x, 8.2 MB 547 / 562, 8.4 MB of 500 entries a row 866 / 968).
   const bool full = (H.rend || H.nnz >= 48 * H.n) &&
-                    (sizeof(XT) == 4 ? b > 2 : b > 8 || (b > 4 && 5 * H.n * ldx <= (int64_t)4 << 20));
+                    (sizeof(XT) == 4 ? b > 2 : b > 8 || (b > 4 && 5 * xb <= 8 * L2));
 #define SPPC_SPMM_CASE(BB, F)                                                                        \
   k_spmm<BB, F, VT, XT><<<grid, 256, 0, s>>>(H.n, H.rp, H.rend, H.col, val, X, ldx, Y, ldy, b, shift, ea, ec, \
                                              eb, Zo, ldz, dg, X64, ldx64);                                 \
@@ -992,9 +994,9 @@ void spmm_panel_rounds(const PanelH& P, const VT* val, const XT* Xc, double* Y, 
 // a workgroup brings each panel of X to LDS (global loads straight to LDS, 1 KB per wave), and its waves take a
 // row block each: a wave goes through the stream of its block, 4 consecutive entries per lane and one batch
 // of 1024 entries ahead, and joins the workgroup's next panel when an entry lies beyond this one (the wait for the
-// panel's loads straight to LDS also waits for the batch ahead), so every wave passes every panel once.  X is read once per workgroup instead of once per entry.  Entries of one
-// row are summed in the lane before their LDS add: with one entry per lane the adds of neighbouring lanes to
-// one row took 60% of the time.  What bounds it now: the latency of a batch per panel, then HBM (n = 772k
+// panel's loads straight to LDS also waits for the batch ahead), so every wave passes every panel once.  X is read
+// once per workgroup instead of once per entry.  Entries of one row are summed in the lane before their LDS add:
+// with one entry per lane the adds of neighbouring lanes to one row took 60% of the time.  What bounds it now: the latency of a batch per panel, then HBM (n = 772k
 // 4.7 TB/s).  us, gathers from L2 / this:
 //   d = 200  n = 1.17M  float64 X 1050 / 612, float32 X 920 / 462, float64 values 1060 / 795;  172k 187 / 175
 //   d = 300  n = 386k 524 / 314, 772k 1018 / 389;  d = 60  n = 305k 107 / 91
@@ -1792,7 +1794,8 @@ void release_panel(PanelH& p) {
 // scratch (the row-wise kernel needs none) and the rows hold enough entries to pay for it and for the passes over
 // the row sums: from 48 entries a row with float64 X (us, row-wise / panel, b = 32: 6 entries n = 150k 59 / 109, 20
 // entries n = 400k 302 / 390, 45 entries n = 1.2M 1883 / 1983, 60 entries n = 1.2M 1.07x, n = 400k 1.19x, 300 entries
-// 1.57x; the odd widths gain more), from 16 with float32 X (b = 27: 6 entries n = 1.2M 546 / 604, 20 entries 1.01 to 1.56x).
+// 1.57x; the odd widths gain more), from 16 with float32 X (b = 27: 6 entries n = 1.2M 546 / 604, 20 entries 1.01 to
+// 1.56x).
 static bool use_panel(const DevCSR& H, int b, const double* shift, const void* stage, size_t stage_bytes,
                       size_t elem) {
   if (!H.panel || shift || b < 1 || b > 32 || H.n <= 0) return false;
