@@ -261,9 +261,9 @@ sppc_status sppc_spmm_upper(const sppc_csr* H, const void* X_dev, sppc_dtype xt,
  * Y = H X exactly as sppc_spmm, for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): this call allocates
  * nothing.  When the context holds the column-panel copy of H and X is not already in the layout
- * its kernels read (b in {1, 2, 4, 8, 16} columns per row, 16-byte aligned), X is copied to a row stride
- * B = 1, 2, 4, 8 or 16 in the library's static device scratch array (32 MiB per device, held until the
- * process ends) instead of the context's buffer; n * B * sizeof(X element) beyond 32 MiB is
+ * its kernels read (b in {1, 2, 4, 8, 16} columns per row, 16-byte aligned) or Y overlaps it, X is copied to
+ * a row stride B = 1, 2, 4, 8 or 16 in the library's static device scratch array (32 MiB per device, held
+ * until the process ends) instead of the context's buffer; n * B * sizeof(X element) beyond 32 MiB is
  * rejected with SPPC_E_ARG (b > 16: the row-wise kernel, which needs no copy, takes the call).  Every
  * call on one device shares that array and it keeps the last call's contents: calls that overlap on one
  * device (several streams or threads) race.
